@@ -1,8 +1,9 @@
 // Host side of the psweep C ABI (include/psweep.h): argument checks, the
 // workspace layout, FP64 level cameras, the per-run job tables and the launch
 // sequence
-//   table upload -> FP64 plane setup -> level images and border marks ->
-//   sweep (one grid per level, or one persistent launch) -> level merge.
+//   table upload -> preparation (plane tables, level images, border marks,
+//   work counters; one launch) -> sweep (one grid per level, or one
+//   persistent launch) -> chunk merge -> level merge.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -18,9 +19,7 @@
 
 using namespace psw;
 
-extern "C" const void *psw_setup_kernel();
 extern "C" const void *psw_prep_kernel();
-extern "C" const void *psw_reset_kernel();
 extern "C" const void *psw_merge_kernel();
 extern "C" const void *psw_chunk_merge_kernel();
 extern "C" const void *psw_filter_kernel();
@@ -871,29 +870,18 @@ psweep_status enqueue(psweep_ctx *ctx, const Blob &blob, char *tb, int which, hi
     PrepDev *dp = (PrepDev *)(tb + blob.preps);
     BorderDev *db = (BorderDev *)(tb + blob.borders);
     MergeDev *dm = (MergeDev *)(tb + blob.merges);
-    int maxPS = 1, maxS = 1;
-    for (int j = 0; j < nj; ++j) {
-        const JobDev &J = (*host_jobs)[j];
-        maxPS = std::max(maxPS, (J.n_fronto + J.n_ground) * J.n_src);
-        maxS = std::max(maxS, J.n_src);
-    }
-    if (do_setup) {
-        void *a[] = {&dsu};
-        PSW_HIP(hipLaunchKernel(psw_setup_kernel(), dim3((maxPS + 255) / 256, nj), dim3(256), a, 0, stream), "setup");
-    }
-    {
-        // level images and the border marks of every job
-        void *a[] = {&dp, &db};
-        PSW_HIP(hipLaunchKernel(psw_prep_kernel(), dim3(256, 1 + maxS, nj), dim3(256), a, 0, stream), "prep");
-    }
+    int maxS = 1;
+    for (int j = 0; j < nj; ++j) maxS = std::max(maxS, (*host_jobs)[j].n_src);
     const int store = cfg.storage, soft = cfg.mode == PSWEEP_MODE_SOFT ? 1 : 0;
     {
-        // the item queues' take counters of every job start at zero (a kernel,
-        // not a memset: the run may be captured into a graph)
+        // plane tables (when they changed), level images, border marks and the
+        // item queues' take counters of every job (zeroed by the kernel, not
+        // by a memset: the run may be captured into a graph)
+        if (!do_setup) dsu = nullptr;
         int *counter = (int *)(ctx->base + ctx->lay->off_counter[which]);
         int n = kQueueHead + kQueues * nj;
-        void *a[] = {&counter, &n};
-        PSW_HIP(hipLaunchKernel(psw_reset_kernel(), dim3(1), dim3(256), a, 0, stream), "reset");
+        void *a[] = {&dp, &db, &dsu, &counter, &n};
+        PSW_HIP(hipLaunchKernel(psw_prep_kernel(), dim3(256, 1 + maxS, nj), dim3(256), a, 0, stream), "prep");
     }
     if (timed) {
         const size_t need = cfg.launch == PSWEEP_LAUNCH_PERSISTENT ? 1 : (size_t)nj;

@@ -1,6 +1,7 @@
-// Small kernels around the sweep: FP64 per-plane setup, level images,
-// border marks, the work counter reset and the level merge; and the static
-// scratch array of psweep_run_noalloc.
+// Small kernels around the sweep: the preparation of a run (FP64 per-plane
+// setup, level images, border marks, work counters), the chunk and level
+// merges, the filter and the mask; and the static scratch array of
+// psweep_run_noalloc.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -11,12 +12,12 @@
 namespace psw {
 
 // ---------------------------------------------------------------------------
-// per-plane parameters in FP64 (H = R + t n^T / d rounded to float)
+// per-plane parameters in FP64 (H = R + t n^T / d rounded to float), by
+// threads t, t + stride, ... of the job's (plane, source) pairs
 // ---------------------------------------------------------------------------
-__global__ void setup_kernel(const SetupDev *__restrict__ jobs) {
-    const SetupDev &J = jobs[blockIdx.y];
+__device__ void plane_setup(const SetupDev &J, int t, int stride) {
     const int P = J.n_fronto + J.n_ground, S = J.n_src;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < P * S; e += gridDim.x * blockDim.x) {
+    for (int e = t; e < P * S; e += stride) {
         const int k = e / S, s = e % S;
         double n[3], d, theta;
         if (k < J.n_fronto) {
@@ -101,14 +102,24 @@ __device__ void border_marks(const BorderDev &B, int t, int stride) {
     }
 }
 
-// blockIdx.z: job; blockIdx.y: 0 = reference level and the job's border
-// marks, 1 + s = source s
-__global__ void prep_kernel(const PrepDev *__restrict__ preps, const BorderDev *__restrict__ borders) {
+// Everything of a run before its sweeps, in one launch: blockIdx.z: job;
+// blockIdx.y: 0 = the job's plane table (setups; NULL when the last run's
+// stands), border marks and reference level, 1 + s = source s; the run's
+// first block also zeroes the item queues' take counters.  The parts share
+// nothing, and a launch of its own costs each small one far more than its
+// work: the counters 1.4-4.6 us and the plane table 2.6-7.3 us on the GPU,
+// beside the gap before the next kernel.
+__global__ void prep_kernel(const PrepDev *__restrict__ preps, const BorderDev *__restrict__ borders,
+                            const SetupDev *__restrict__ setups, int *__restrict__ counters, int n_counters) {
     const PrepDev &P = preps[blockIdx.z];
     const int which = blockIdx.y;
     const int ds = P.downsample;
     if (which == 0) {
-        border_marks(borders[blockIdx.z], blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+        const int t0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+        if (blockIdx.x == 0 && blockIdx.z == 0)
+            for (int i = threadIdx.x; i < n_counters; i += blockDim.x) counters[i] = 0;
+        if (setups) plane_setup(setups[blockIdx.z], t0, stride);
+        border_marks(borders[blockIdx.z], t0, stride);
         if (!P.ref_level) return;
         const int lw = P.ref_w / ds, lh = P.ref_h / ds;
         for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < lw * lh; e += gridDim.x * blockDim.x) {
@@ -167,10 +178,6 @@ __global__ void prep_kernel(const PrepDev *__restrict__ preps, const BorderDev *
         const uint32_t p01 = level_pix(img, pitch, x, y1, ds), p11 = level_pix(img, pitch, x1, y1, ds);
         tex[e] = coef_texel(p00, p10, p01, p11);
     }
-}
-
-__global__ void reset_counter_kernel(int *counter, int n) {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) counter[i] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -400,8 +407,6 @@ extern "C" {
 const void *psw_filter_kernel() { return (const void *)&psw::filter_kernel; }
 const void *psw_mask_kernel() { return (const void *)&psw::mask_kernel; }
 const void *psw_chunk_merge_kernel() { return (const void *)&psw::chunk_merge_kernel; }
-const void *psw_setup_kernel() { return (const void *)&psw::setup_kernel; }
 const void *psw_prep_kernel() { return (const void *)&psw::prep_kernel; }
-const void *psw_reset_kernel() { return (const void *)&psw::reset_counter_kernel; }
 const void *psw_merge_kernel() { return (const void *)&psw::merge_kernel; }
 }
