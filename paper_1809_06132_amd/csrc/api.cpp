@@ -252,7 +252,7 @@ psweep_status check_config(const psweep_config *c) {
 
 struct Blob {
     std::vector<char> bytes;
-    size_t jobs = 0, setups = 0, preps = 0, borders = 0, merges = 0, orders = 0;
+    size_t jobs = 0, setups = 0, preps = 0, borders = 0, merges = 0, orders = 0;   // orders: or the run's queues
     int nj = 0, nm = 0;
 };
 
@@ -281,7 +281,7 @@ Layout make_layout(const psweep_config &cfg, const int *P, const int *ref_w, con
                     align_up(sizeof(MergeDev) * kMaxJobs) + order_bytes;
     size_t off = 0;
     for (int g = 0; g < 2; ++g) { L.off_table[g] = off; off += L.table_bytes; }
-    for (int g = 0; g < 2; ++g) { L.off_counter[g] = off; off += align_up(sizeof(int) * (kQueueHead + kQueues * kMaxJobs)); }
+    for (int g = 0; g < 2; ++g) { L.off_counter[g] = off; off += align_up(sizeof(int) * kQueues * kCounterStride); }
     L.off_slots = off;
     size_t so = 0;
     const int S = cfg.max_sources;
@@ -543,15 +543,28 @@ psweep_status psweep_plane_pixels_met(const psweep_ctx *ctx, const psweep_frame 
 
 namespace {
 
-// The item queues of one job (see JobDev::order): tile row y goes to queue
-// y mod 8, one queue per XCD, so that an XCD's L2 holds the source texels of
-// its rows; each queue is sorted largest item first, the size of an item
-// being its (pixel, plane) pairs that meet their plane (the pixels of its
-// tile whose Eq. (1) ray meets the chunk's family, times the chunk's planes;
-// FP64 on the host).  Long items then start first and short ones fill the
-// end of the launch, instead of a long one starting last; ties keep the
-// chunk-major order.  Depends only on the level's geometry and the launch
-// shape: cached.
+// The items of one job, dealt out over the XCDs: tile row y goes to XCD y mod 8,
+// so that an XCD's L2 holds the source texels of its rows.  Depends only on the
+// level's geometry and the launch shape: cached.
+//
+// Grid launch: the item of every workgroup (see JobDev::order).  Each XCD's
+// items are sorted largest first, which shortens the launch's tail (long items
+// start first and short ones fill its end), the size of an item being its
+// (pixel, plane) pairs that meet their plane (the pixels of its tile whose
+// Eq. (1) ray meets the chunk's family, times the chunk's planes; FP64 on the
+// host, from every fourth row and column: a size decides the order and nothing
+// else); ties keep the chunk-major order.  Workgroup b runs on XCD b mod 8 and
+// takes the next item of that XCD, or the next of the XCD with the most left
+// once its own are dealt.  A fixed order, because each of the queues' counters
+// that the workgroups used to take their items from cost a round trip at every
+// workgroup's start and served them one at a time (320x256, one source, 768
+// workgroups: the sweep took 27 us, and 19 us dealt).
+//
+// Persistent launch: the eight XCDs' queues one after another, behind their
+// nine starts, each row by row, every chunk of a tile row before the next row,
+// so that the workgroups resident on an XCD work on neighbouring source
+// footprints that its L2 holds (measured faster on one-level, two-level and
+// batched workloads alike).
 const std::vector<int32_t> &item_order(psweep_ctx *ctx, const LevelCam &rc, const psweep_level &L,
                                        const JobDev &J) {
     const psweep_config &cfg = ctx->cfg;
@@ -561,13 +574,26 @@ const std::vector<int32_t> &item_order(psweep_ctx *ctx, const LevelCam &rc, cons
                                      (double)J.waves, (double)J.nch_f, (double)J.nch_g};
     auto it = ctx->order_cache.find(key);
     if (it != ctx->order_cache.end()) return it->second;
-    const int hw = L.window / 2, txo = kWave - 2 * hw, tyo = J.rows * J.waves;
     const int ntile = J.tiles_x * J.tiles_y;
+    const int nch = std::max(1, J.nch_f + J.nch_g);
+    std::vector<int32_t> order;
+    if (cfg.launch == PSWEEP_LAUNCH_PERSISTENT) {
+        order.assign(kQueueHead, 0);
+        for (int q = 0; q < kQueues; ++q) {
+            order[q] = (int32_t)(order.size() - kQueueHead);
+            for (int y = q; y < J.tiles_y; y += kQueues)
+                for (int c = 0; c < nch; ++c)
+                    for (int x = 0; x < J.tiles_x; ++x) order.push_back(c * ntile + y * J.tiles_x + x);
+        }
+        order[kQueues] = (int32_t)(order.size() - kQueueHead);
+        return ctx->order_cache.emplace(key, std::move(order)).first->second;
+    }
+    const int hw = L.window / 2, txo = kWave - 2 * hw, tyo = J.rows * J.waves;
     std::vector<int64_t> met_f(ntile, 0), met_g(ntile, 0);
-    for (int j = hw; j < rc.h - hw; ++j) {
+    for (int j = hw; j < rc.h - hw; j += 4) {
         const double y = (j - rc.cy) / rc.fy;
         const int trow = ((j - hw) / tyo) * J.tiles_x;
-        for (int i = hw; i < rc.w - hw; ++i) {
+        for (int i = hw; i < rc.w - hw; i += 4) {
             const double x = (i - rc.cx) / rc.fx;
             const double q = x * x + y * y;
             const double eta = (rc.xi + std::sqrt(1.0 + (1.0 - rc.xi * rc.xi) * q)) / (q + 1.0);
@@ -577,7 +603,6 @@ const std::vector<int32_t> &item_order(psweep_ctx *ctx, const LevelCam &rc, cons
             met_g[t] += cfg.ground_n[0] * eta * x + cfg.ground_n[1] * eta * y + cfg.ground_n[2] * rz > 0.0;
         }
     }
-    const int nch = std::max(1, J.nch_f + J.nch_g);
     std::vector<int64_t> weight((size_t)nch * ntile);
     for (int c = 0; c < nch; ++c) {
         int kb = 0, ke = L.n_fronto + L.n_ground;
@@ -586,37 +611,33 @@ const std::vector<int32_t> &item_order(psweep_ctx *ctx, const LevelCam &rc, cons
         const int64_t pg = std::max(0, ke - std::max(kb, L.n_fronto));
         for (int t = 0; t < ntile; ++t) weight[(size_t)c * ntile + t] = met_f[t] * pf + met_g[t] * pg;
     }
-    // Grid launch: each queue largest item first, which shortens the launch's
-    // tail.  Persistent launch: each queue row by row, every chunk of a tile
-    // row before the next row, so that the workgroups resident on an XCD work
-    // on neighbouring source footprints that its L2 holds (measured faster on
-    // one-level, two-level and batched workloads alike).
-    const bool by_row = cfg.launch == PSWEEP_LAUNCH_PERSISTENT;
-    std::vector<int32_t> order(kQueueHead, 0);
+    std::vector<int32_t> share[kQueues];
     for (int q = 0; q < kQueues; ++q) {
-        order[q] = (int32_t)(order.size() - kQueueHead);
-        const size_t lo = order.size();
-        if (by_row) {
+        for (int c = 0; c < nch; ++c)
             for (int y = q; y < J.tiles_y; y += kQueues)
-                for (int c = 0; c < nch; ++c)
-                    for (int x = 0; x < J.tiles_x; ++x) order.push_back(c * ntile + y * J.tiles_x + x);
-        } else {
-            for (int c = 0; c < nch; ++c)
-                for (int y = q; y < J.tiles_y; y += kQueues)
-                    for (int x = 0; x < J.tiles_x; ++x) order.push_back(c * ntile + y * J.tiles_x + x);
-            std::stable_sort(order.begin() + lo, order.end(),
-                             [&](int32_t a, int32_t b) { return weight[a] > weight[b]; });
-        }
+                for (int x = 0; x < J.tiles_x; ++x) share[q].push_back(c * ntile + y * J.tiles_x + x);
+        std::stable_sort(share[q].begin(), share[q].end(),
+                         [&](int32_t a, int32_t b) { return weight[a] > weight[b]; });
     }
-    order[kQueues] = (int32_t)(order.size() - kQueueHead);
+    size_t at[kQueues] = {};
+    const size_t n = (size_t)ntile * nch;
+    order.reserve(n);
+    while (order.size() < n) {
+        int q = (int)(order.size() % kQueues);
+        if (at[q] == share[q].size())
+            for (int o = 0; o < kQueues; ++o)
+                if (share[o].size() - at[o] > share[q].size() - at[q]) q = o;
+        order.push_back(share[q][at[q]++]);
+    }
     return ctx->order_cache.emplace(key, std::move(order)).first->second;
 }
 
 // Build the per-run tables (host side) for `frames`: job, setup, prep,
-// border and merge records and the jobs' item orders, packed at fixed
-// offsets of one blob that is uploaded to device address `tb`.
+// border and merge records and the jobs' item orders (or, for a persistent
+// launch, the run's item queues), packed at fixed offsets of one blob that is
+// uploaded to device address `tb`.
 psweep_status build_tables(psweep_ctx *ctx, const psweep_frame *frames, int nf, const psweep_output *out,
-                           char *tb, int *counters, Blob &blob, std::vector<int> &job_frame) {
+                           char *tb, Blob &blob, std::vector<int> &job_frame) {
     const psweep_config &cfg = ctx->cfg;
     const int NL = cfg.n_levels;
     const bool sf = single_full(cfg);
@@ -627,7 +648,6 @@ psweep_status build_tables(psweep_ctx *ctx, const psweep_frame *frames, int nf, 
     std::vector<MergeDev> merges;
     std::vector<const std::vector<int32_t> *> orders;   // map nodes: stable while the run is built
     if (ctx->order_cache.size() > 192) ctx->order_cache.clear();   // one run adds at most kMaxJobs
-    int first_item = 0;
     for (int f = 0; f < nf; ++f) {
         const psweep_frame &fr = frames[f];
         const int csi = fr.camera_set;
@@ -749,11 +769,7 @@ psweep_status build_tables(psweep_ctx *ctx, const psweep_frame *frames, int nf, 
                     if (J.nch_f + J.nch_g <= 1) { J.nch_f = 0; J.nch_g = 0; }
                 }
                 J.part = (float *)(slot + Y.s_part[l]);
-                const int items = ntile * std::max(1, J.nch_f + J.nch_g);
-                J.first_item = first_item;
-                first_item += items;
                 orders.push_back(&item_order(ctx, rc, L, J));
-                J.queue_ctr = counters + kQueueHead + kQueues * (int)orders.size() - kQueues;
             }
             for (int s = 0; s < C.n_src; ++s) {
                 const LevelCam sc = level_cam(C.src[s], ds, 0, 0, 0, 0);
@@ -843,15 +859,34 @@ psweep_status build_tables(psweep_ctx *ctx, const psweep_frame *frames, int nf, 
     blob.merges = blob.borders + align_up(sizeof(BorderDev) * nj);
     blob.orders = blob.merges + align_up(sizeof(MergeDev) * (nm > 0 ? nm : 1));
     size_t total = blob.orders;
+    const bool queues = cfg.launch == PSWEEP_LAUNCH_PERSISTENT;
+    size_t n_items = 0;
     for (int j = 0; j < nj; ++j) {
+        if (queues) { n_items += orders[j]->size() - kQueueHead; continue; }
         jobs[j].order = (const int32_t *)(tb + total);
         total += align_up(sizeof(int32_t) * orders[j]->size());
     }
+    if (queues) total += align_up(sizeof(int32_t) * (kQueueHead + n_items));
     if (total > ctx->lay->table_bytes) return fail(ctx, PSWEEP_EINVAL, "too many frames for the table region");
     blob.bytes.assign(total, 0);
-    for (int j = 0; j < nj; ++j)
-        std::memcpy(blob.bytes.data() + ((const char *)jobs[j].order - tb), orders[j]->data(),
-                    sizeof(int32_t) * orders[j]->size());
+    if (queues) {
+        // the run's queues: every job's share of an XCD, job after job
+        int32_t *head = reinterpret_cast<int32_t *>(blob.bytes.data() + blob.orders), *out_item = head + kQueueHead;
+        for (int q = 0; q < kQueues; ++q) {
+            head[q] = (int32_t)(out_item - head) - kQueueHead;
+            for (int j = 0; j < nj; ++j) {
+                const std::vector<int32_t> &o = *orders[j];
+                const uint32_t job = (uint32_t)j << kItemBits;
+                for (int32_t i = o[q]; i < o[q + 1]; ++i)
+                    *out_item++ = (int32_t)(job | (uint32_t)o[kQueueHead + i]);
+            }
+        }
+        head[kQueues] = (int32_t)(out_item - head) - kQueueHead;
+    } else {
+        for (int j = 0; j < nj; ++j)
+            std::memcpy(blob.bytes.data() + ((const char *)jobs[j].order - tb), orders[j]->data(),
+                        sizeof(int32_t) * orders[j]->size());
+    }
     std::memcpy(blob.bytes.data() + blob.jobs, jobs.data(), sizeof(JobDev) * nj);
     std::memcpy(blob.bytes.data() + blob.setups, setups.data(), sizeof(SetupDev) * nj);
     std::memcpy(blob.bytes.data() + blob.preps, preps.data(), sizeof(PrepDev) * nj);
@@ -874,12 +909,12 @@ psweep_status enqueue(psweep_ctx *ctx, const Blob &blob, char *tb, int which, hi
     for (int j = 0; j < nj; ++j) maxS = std::max(maxS, (*host_jobs)[j].n_src);
     const int store = cfg.storage, soft = cfg.mode == PSWEEP_MODE_SOFT ? 1 : 0;
     {
-        // plane tables (when they changed), level images, border marks and the
-        // item queues' take counters of every job (zeroed by the kernel, not
-        // by a memset: the run may be captured into a graph)
+        // plane tables (when they changed), level images and border marks of
+        // every job, and a persistent launch's take counters (zeroed by the
+        // kernel, not by a memset: the run may be captured into a graph)
         if (!do_setup) dsu = nullptr;
         int *counter = (int *)(ctx->base + ctx->lay->off_counter[which]);
-        int n = kQueueHead + kQueues * nj;
+        int n = cfg.launch == PSWEEP_LAUNCH_PERSISTENT ? kQueues * kCounterStride : 0;
         void *a[] = {&dp, &db, &dsu, &counter, &n};
         PSW_HIP(hipLaunchKernel(psw_prep_kernel(), dim3(256, 1 + maxS, nj), dim3(256), a, 0, stream), "prep");
     }
@@ -904,8 +939,8 @@ psweep_status enqueue(psweep_ctx *ctx, const Blob &blob, char *tb, int which, hi
             if (!kern[j]) return fail(ctx, PSWEEP_EUNSUPPORTED, "no kernel for this window/tile/sources/storage");
             ++n_launch;
         }
-        // Jobs share nothing they write (maps, partial states, queue
-        // counters are per job), so consecutive ones go to the caller's
+        // Jobs share nothing they write (maps and partial states are
+        // per job), so consecutive ones go to the caller's
         // stream and the side stream in turn: a job's tail then overlaps the
         // next job's start.  Both streams join the caller's before the merges.
         const bool two = n_launch > 1 && ctx->side_stream;
@@ -953,9 +988,8 @@ psweep_status enqueue(psweep_ctx *ctx, const Blob &blob, char *tb, int which, hi
         if (per_cu < 1) per_cu = 1;
         const int grid = std::min(n_items, n_cu * per_cu);
         if (grid > 0) {
-            void *a[] = {&dj, (void *)&nj, &n_items, &counter};
-            int nj_v = nj;
-            a[1] = &nj_v;
+            int32_t *queues = (int32_t *)(tb + blob.orders);
+            void *a[] = {&dj, &queues, &counter};
             if (timed) PSW_HIP(hipEventRecord(ctx->ev0[0], stream), "event record");
             PSW_HIP(hipLaunchKernel(e->fn, dim3(grid), dim3(kWave * ctx->tile_waves[0]), a, e->lds, stream), "sweep");
             if (timed) { PSW_HIP(hipEventRecord(ctx->ev1[0], stream), "event record"); ctx->n_timed = 1; }
@@ -1012,7 +1046,7 @@ psweep_status run_on(psweep_ctx *ctx, const psweep_frame *frames, int32_t n_fram
     Blob blob;
     std::vector<int> job_frame;
     char *tb = base + lay->off_table[0];
-    psweep_status st = build_tables(ctx, frames, n_frames, out, tb, (int *)(base + lay->off_counter[0]), blob, job_frame);
+    psweep_status st = build_tables(ctx, frames, n_frames, out, tb, blob, job_frame);
     if (st != PSWEEP_OK) return st;
     std::vector<JobDev> hj(blob.nj);
     std::memcpy(hj.data(), blob.bytes.data() + blob.jobs, sizeof(JobDev) * blob.nj);
@@ -1127,8 +1161,7 @@ psweep_status psweep_graph_capture(psweep_ctx *ctx, const psweep_frame *frames, 
     ctx->base = ctx->ws;
     ctx->lay = &ctx->full;
     char *tb = ctx->ws + ctx->full.off_table[1];
-    psweep_status st =
-        build_tables(ctx, frames, n_frames, out, tb, (int *)(ctx->ws + ctx->full.off_counter[1]), blob, job_frame);
+    psweep_status st = build_tables(ctx, frames, n_frames, out, tb, blob, job_frame);
     if (st != PSWEEP_OK) return st;
     std::vector<JobDev> hj(blob.nj);
     std::memcpy(hj.data(), blob.bytes.data() + blob.jobs, sizeof(JobDev) * blob.nj);

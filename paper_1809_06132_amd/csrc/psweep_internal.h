@@ -45,7 +45,7 @@ struct JobDev {
     int64_t out_pitch;
     float *soft_rho, *soft_lse;
     int64_t soft_pitch;
-    int32_t tiles_x, tiles_y, first_item, pad0;
+    int32_t tiles_x, tiles_y, pad0, pad5;
     // tile shape used for this job by the grid launch (rows per wave, waves)
     int32_t rows, waves, pad1, pad2;
     // plane chunks: the fronto planes are cut into nch_f contiguous chunks and
@@ -54,18 +54,23 @@ struct JobDev {
     // chunk_merge_kernel combines
     int32_t nch_f, nch_g, pad3, pad4;
     float *part;           // [chunk][word][h][w], pitch w
-    // The job's (chunk, tile) items (chunk * tiles + tile) in eight queues,
-    // one per XCD: order[0 .. 8] are the queues' starts in order + kQueueHead
-    // (order[8]: the item count), each queue sorted largest item first;
-    // queue_ctr: the eight queues' take counters (zeroed before the launch).
+    // Grid launch: the (chunk, tile) item (chunk * tiles + tile) of every
+    // workgroup.  (A persistent launch has one set of queues for the run.)
     const int32_t *order;
-    int32_t *queue_ctr;
     float *volume;         // optional [P][h][w] aggregated costs (psweep_output::cost_volume)
     SrcDev src[kMaxSrc];
 };
 
-constexpr int kQueueHead = 16;   // ints before the items of an order table
 constexpr int kQueues = 8;       // one item queue per XCD
+// The run-wide queues of a persistent launch: kQueueHead words of which the
+// first nine are the queues' starts among the items (the ninth: the item
+// count), then the items, job << kItemBits | item, queue after queue.
+constexpr int kQueueHead = 16;
+constexpr int kItemBits = 26;    // 64 jobs; the largest frame has under 2^22 items a level
+constexpr uint32_t kNoItem = 0xffffffffu;
+// ints from one queue's take counter to the next: a cache line each, since
+// atomics on one line are served one after another (about 80 ns each)
+constexpr int kCounterStride = 32;
 constexpr int kPartWords = 7;   // c1, kb, c2, cm, cp, first, last (soft: max, sum, sum*theta)
 constexpr int kMaxChunks = 8;
 
@@ -82,7 +87,7 @@ __host__ __device__ inline void chunk_range(int n_fronto, int n_ground, int nch_
     }
 }
 
-// FP64 description of one (frame, level) for the setup kernel.
+// FP64 description of one (frame, level) for the plane setup.
 struct SetupDev {
     double R[kMaxSrc][9];
     double t[kMaxSrc][3];

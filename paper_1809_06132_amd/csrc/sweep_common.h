@@ -829,30 +829,13 @@ constexpr int sweep_waves_per_eu() { return R == 4 && NW == 4 && WIN <= 9 && STO
 template <int WIN, int R, int NW, int S, int STORE, bool SOFT, int IMG = 0>
 __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(sweep_waves_per_eu<WIN, R, NW, S, STORE>())))
 void sweep_grid_kernel(const JobDev *__restrict__ job) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];   // after the static LDS, 16-byte aligned
+    extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tx = job->tiles_x;
-    // Blocks go to the eight XCDs round-robin (block b to XCD b % 8), and
-    // every XCD has a queue of items (its share of the tile rows, so that
-    // its L2 holds the source texels those rows reach; largest item first).
-    // A block takes the next item of its XCD's queue, or of the next queue
-    // that has items left when its own is empty, so the XCDs finish together.
-    // There are as many blocks as items: every block takes exactly one.
-    __shared__ int item_s;
-    if (threadIdx.x == 0) {
-        const PSW_CONST int32_t *hd = cptr(job->order);
-        int it = -1;
-        for (int a = 0; a < kQueues && it < 0; ++a) {
-            const int q = (blockIdx.x + a) & (kQueues - 1);
-            const int lo = hd[q], n = hd[q + 1] - lo;
-            if (n <= 0) continue;
-            const int c = atomicAdd(job->queue_ctr + q, 1);
-            if (c < n) it = hd[kQueueHead + lo + c];
-        }
-        item_s = it;
-    }
-    __syncthreads();
-    const int item = __builtin_amdgcn_readfirstlane(item_s);   // uniform: the tile stays scalar
-    if (item < 0) return;
+    // Blocks go to the eight XCDs round-robin (block b to XCD b % 8), and the
+    // job's order deals the items out to them so: item b belongs to XCD b % 8's
+    // share of the tile rows (its L2 then holds the source texels those rows
+    // reach), largest items first.  There are as many blocks as items.
+    const int item = cptr(job->order)[blockIdx.x];
     const int ntile = tx * job->tiles_y;
     const int chunk = item / ntile;
     const int tile = item - chunk * ntile;
@@ -882,40 +865,54 @@ __device__ __forceinline__ int opaque_lane() {
 }
 
 // One persistent launch for every (frame, level, tile) of a run: workgroups
-// take (chunk, tile) items job after job, from their XCD's queue of the job
-// (or the next queue with items left), until every job is exhausted; every
-// workgroup then leaves.
+// take (job, chunk, tile) items from their XCD's queue, then from whichever
+// queue has items left, until all are empty; every workgroup then leaves.
+// Workgroup b's first item is item b / 8 of queue b % 8, without an atomic
+// (1,024 workgroups starting at once would wait about 10 us for their turns at
+// the counters).  Later items of its own queue cost one atomic each; of the
+// other queues, a counter is read first and an atomic goes only to a queue that
+// still has items, so that the workgroups' last look around is loads, which
+// are served together, and not atomics, one after another.
 template <int R, int NW, int S, int STORE>
-__global__ __launch_bounds__(kWave *NW) void sweep_persistent_kernel(const JobDev *__restrict__ jobs, int n_jobs,
-                                                                     int n_items, int *counter) {
+__global__ __launch_bounds__(kWave *NW) void sweep_persistent_kernel(const JobDev *__restrict__ jobs,
+                                                                     const int32_t *__restrict__ queues,
+                                                                     int *__restrict__ counters) {
     extern __shared__ __attribute__((aligned(16))) char smem[];   // after the static LDS, 16-byte aligned
-    __shared__ int item_s, job_s;
-    (void)n_items;
-    (void)counter;
-    int j = 0;
+    __shared__ uint32_t item_s;
+    // -1: the first item; else the queue to take from next (own first).  In
+    // LDS: as a register across the tile it takes the kernel past 128 VGPRs.
+    __shared__ int next_s;
+    if (threadIdx.x == 0) next_s = -1;
     for (;;) {
         if (threadIdx.x == 0) {
-            int it = -1;
-            while (j < n_jobs && it < 0) {
-                const PSW_CONST int32_t *hd = cptr(jobs[j].order);
-                for (int a = 0; a < kQueues && it < 0; ++a) {
-                    const int q = (blockIdx.x + a) & (kQueues - 1);
-                    const int lo = hd[q], n = hd[q + 1] - lo;
-                    if (n <= 0) continue;
-                    const int c = atomicAdd(jobs[j].queue_ctr + q, 1);
-                    if (c < n) it = hd[kQueueHead + lo + c];
+            const PSW_CONST int32_t *hd = cptr(queues);
+            uint32_t it = kNoItem;
+            int next = next_s;
+            if (next < 0) {
+                const int q0 = blockIdx.x % kQueues, at = hd[q0] + (int)(blockIdx.x / kQueues);
+                if (at < hd[q0 + 1]) it = (uint32_t)hd[kQueueHead + at];
+                next = 0;
+            }
+            while (next < kQueues && it == kNoItem) {
+                const int q = (blockIdx.x + next) & (kQueues - 1);
+                // the blocks' first items are not counted by the counter
+                const int at = hd[q] + ((int)gridDim.x - q + kQueues - 1) / kQueues, n = hd[q + 1] - at;
+                int *ctr = counters + q * kCounterStride;
+                if (n > 0 && (next == 0 || __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n)) {
+                    const int c = atomicAdd(ctr, 1);
+                    if (c < n) it = (uint32_t)hd[kQueueHead + at + c];
                 }
-                if (it < 0) ++j;
+                if (it == kNoItem) ++next;
             }
             item_s = it;
-            job_s = j;
+            next_s = next;
         }
         __syncthreads();
         // the same for every lane: uniform, so the tile's values stay scalar
-        const int t = __builtin_amdgcn_readfirstlane(item_s);
-        j = __builtin_amdgcn_readfirstlane(job_s);
+        const uint32_t take = (uint32_t)__builtin_amdgcn_readfirstlane((int)item_s);
         __syncthreads();
-        if (t < 0) break;
+        if (take == kNoItem) break;
+        const int j = (int)(take >> kItemBits), t = (int)(take & ((1u << kItemBits) - 1));
         const JobDev *J = jobs + j;
         const int ntile = J->tiles_x * J->tiles_y;
         const int tile = t % ntile, chunk = t / ntile;
