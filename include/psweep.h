@@ -68,6 +68,9 @@ typedef enum {
 
 enum { PSWEEP_STORAGE_F32 = 0, PSWEEP_STORAGE_F16 = 1, PSWEEP_STORAGE_BF16 = 2 };
 enum { PSWEEP_MODE_WTA = 0, PSWEEP_MODE_SOFT = 1 };
+/* How a run's sweeps are launched (the maps do not depend on it): GRID takes
+ * every config and may sweep a run's jobs in one persistent launch where that
+ * is faster; PERSISTENT always does, and refuses what it has no kernel for. */
 enum { PSWEEP_LAUNCH_GRID = 0, PSWEEP_LAUNCH_PERSISTENT = 1 };
 /* Pixel type of the frame images: 8-bit grey levels, or 32-bit float grey
  * values (any real values; the cost is invariant to affine intensity changes
@@ -210,11 +213,10 @@ psweep_status psweep_run(psweep_ctx *ctx, const psweep_frame *frames, int32_t n_
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same maps, bitwise, with no workspace.  The run's scratch (job tables,
  * counters, level images, textures, level maps) lives in a static device
- * array of the library, 64 MiB per GPU, held until the process ends; each
- * tile sweeps all its planes in one pass (no plane chunks, which would need
- * partial-state room).  The caller passes only inputs and outputs; no
- * psweep_set_workspace is needed.  EINVAL (with the bytes the context needs)
- * when the context's limits (max_width x max_height, max_sources,
+ * array of the library, 64 MiB per GPU, held until the process ends; the
+ * planes are cut into as many chunks as it has room for.  The caller passes
+ * only inputs and outputs; no psweep_set_workspace is needed.  EINVAL (with
+ * the bytes the context needs) when the context's limits (max_width x max_height, max_sources,
  * max_frames) need more than 64 MiB, e.g. one 1024 x 768 frame with three
  * sources needs about 31 MiB; EUNSUPPORTED in soft mode.  Every call on one
  * GPU shares that GPU's array, which keeps the last call's contents: calls
@@ -328,8 +330,8 @@ psweep_status psweep_set_timing(psweep_ctx *ctx, int32_t on);
 psweep_status psweep_sweep_kernel_ms(psweep_ctx *ctx, double *ms, int32_t *n_launches);
 
 /* Durations in milliseconds of each sweep kernel launch of the last run, in
- * launch order (one per (frame, level) with the grid launch, one for the
- * persistent launch); at most `capacity` values, *n receives the count. */
+ * launch order (one per (frame, level) with the grid launch, which a timed run
+ * of a GRID config always uses, one for the persistent launch); at most `capacity` values, *n receives the count. */
 psweep_status psweep_sweep_kernel_times(psweep_ctx *ctx, double *ms, int32_t capacity, int32_t *n);
 
 /* Plane-pixel evaluations (pixels x planes, all levels, all frames) of one

@@ -109,7 +109,7 @@ struct Layout {
     size_t s_ref[PSWEEP_MAX_LEVELS] = {0, 0}, s_tex[PSWEEP_MAX_LEVELS] = {0, 0}, s_maps[PSWEEP_MAX_LEVELS] = {0, 0},
            s_htab[PSWEEP_MAX_LEVELS] = {0, 0}, s_theta[PSWEEP_MAX_LEVELS] = {0, 0}, s_part[PSWEEP_MAX_LEVELS] = {0, 0};
     size_t need = 0;
-    bool parts = true;   // room for plane-chunk partial states
+    int part_chunks = kMaxChunks;   // plane chunks whose partial states have room (under 2: none)
 };
 }  // namespace
 
@@ -140,6 +140,7 @@ struct psweep_ctx {
     int tile_rows[PSWEEP_MAX_LEVELS] = {4, 4}, tile_waves[PSWEEP_MAX_LEVELS] = {4, 4};
     int chunks[PSWEEP_MAX_LEVELS] = {0, 0};   // plane chunks per tile; 0 = automatic
     int n_cu = 256;
+    std::map<const KernelEntry *, int> resident;   // see resident_blocks
     // timing of sweep launches
     bool timing = false;
     std::vector<hipEvent_t> ev0, ev1;
@@ -254,6 +255,8 @@ struct Blob {
     std::vector<char> bytes;
     size_t jobs = 0, setups = 0, preps = 0, borders = 0, merges = 0, orders = 0;   // orders: or the run's queues
     int nj = 0, nm = 0;
+    bool queues = false;                   // one launch over item queues, not a grid per job
+    const KernelEntry *kernel = nullptr;   // that launch's kernel
 };
 
 // Largest number of (chunk, tile) items of one job on level l of a config:
@@ -267,10 +270,13 @@ size_t max_items(const psweep_config &c, int l, int w, int h) {
     return tx * ty * kMaxChunks;
 }
 
+// The layout of a run's scratch.  limit 0: with partial states for every plane
+// chunk.  Else `need` counts none, and the bytes left below the limit hold
+// those of as many chunks as fit; a single full-resolution level writes its
+// maps straight to the caller, so there the room for level maps serves too.
 Layout make_layout(const psweep_config &cfg, const int *P, const int *ref_w, const int *ref_h, const int *src_w,
-                   const int *src_h, bool parts) {
+                   const int *src_h, size_t limit) {
     Layout L;
-    L.parts = parts;
     // table region: every kind of record for kMaxJobs jobs, and the item queues
     size_t order_bytes = 0;
     for (int l = 0; l < cfg.n_levels; ++l)
@@ -293,10 +299,31 @@ Layout make_layout(const psweep_config &cfg, const int *P, const int *ref_w, con
         L.s_maps[l] = so;  so += align_up(rpx * 4) * 4;
         L.s_htab[l] = so;  so += align_up((size_t)P[l] * S * 9 * 4);
         L.s_theta[l] = so; so += align_up((size_t)P[l] * 4);
-        L.s_part[l] = so;  so += parts ? align_up(rpx * 4 * kPartWords * kMaxChunks) : 0;
+        L.s_part[l] = so;  so += limit ? 0 : align_up(rpx * 4 * kPartWords * kMaxChunks);
     }
     L.slot_bytes = align_up(so);
     L.need = L.off_slots + L.slot_bytes * cfg.max_frames;
+    if (!limit) return L;
+    // every frame's share of what is left, as far as its chunks reach
+    const size_t left = L.need < limit ? (limit - L.need) / cfg.max_frames / kAlign * kAlign : 0;
+    const size_t spare = single_full(cfg) ? align_up((size_t)ref_w[0] * ref_h[0] * 4) * 4 : 0;
+    size_t chunk_bytes = 0;
+    for (int l = 0; l < cfg.n_levels; ++l) chunk_bytes += align_up((size_t)ref_w[l] * ref_h[l] * 4 * kPartWords);
+    L.part_chunks = (int)std::min<size_t>(kMaxChunks, (left + spare) / chunk_bytes);
+    if (L.part_chunks < 2) return L;
+    if (spare) {
+        // the maps end the slot but for the two plane tables: put those first
+        L.s_htab[0] = L.s_maps[0];
+        L.s_theta[0] = L.s_htab[0] + align_up((size_t)P[0] * S * 9 * 4);
+        L.s_part[0] = L.s_theta[0] + align_up((size_t)P[0] * 4);
+        so = L.s_part[0] + align_up((size_t)ref_w[0] * ref_h[0] * 4 * kPartWords) * L.part_chunks;
+    } else {
+        for (int l = 0; l < cfg.n_levels; ++l) {
+            L.s_part[l] = so;
+            so += align_up((size_t)ref_w[l] * ref_h[l] * 4 * kPartWords) * L.part_chunks;
+        }
+    }
+    L.slot_bytes = std::max(L.slot_bytes, align_up(so));
     return L;
 }
 
@@ -329,8 +356,9 @@ psweep_status psweep_create(const psweep_config *cfg, psweep_ctx **out) {
         ctx->ref_w[l] = ctx->src_w[l];
         ctx->ref_h[l] = ctx->src_h[l];
     }
-    ctx->full = make_layout(*cfg, ctx->P, ctx->ref_w, ctx->ref_h, ctx->src_w, ctx->src_h, true);
-    ctx->lean = make_layout(*cfg, ctx->P, ctx->ref_w, ctx->ref_h, ctx->src_w, ctx->src_h, false);
+    ctx->full = make_layout(*cfg, ctx->P, ctx->ref_w, ctx->ref_h, ctx->src_w, ctx->src_h, 0);
+    ctx->lean = make_layout(*cfg, ctx->P, ctx->ref_w, ctx->ref_h, ctx->src_w, ctx->src_h,
+                            kStaticScratchBytes);
     for (int b = 0; b < 2; ++b) {
         if (hipHostMalloc((void **)&ctx->staging[b], ctx->full.table_bytes, hipHostMallocDefault) != hipSuccess ||
             hipEventCreateWithFlags(&ctx->staging_ev[b], hipEventDisableTiming) != hipSuccess) {
@@ -566,18 +594,18 @@ namespace {
 // footprints that its L2 holds (measured faster on one-level, two-level and
 // batched workloads alike).
 const std::vector<int32_t> &item_order(psweep_ctx *ctx, const LevelCam &rc, const psweep_level &L,
-                                       const JobDev &J) {
+                                       const JobDev &J, bool queues) {
     const psweep_config &cfg = ctx->cfg;
     const std::vector<double> key = {rc.xi, rc.fx, rc.fy, rc.cx, rc.cy, (double)rc.w, (double)rc.h,
                                      (double)L.window, (double)L.n_fronto, (double)L.n_ground,
                                      cfg.ground_n[0], cfg.ground_n[1], cfg.ground_n[2], (double)J.rows,
-                                     (double)J.waves, (double)J.nch_f, (double)J.nch_g};
+                                     (double)J.waves, (double)J.nch_f, (double)J.nch_g, (double)queues};
     auto it = ctx->order_cache.find(key);
     if (it != ctx->order_cache.end()) return it->second;
     const int ntile = J.tiles_x * J.tiles_y;
     const int nch = std::max(1, J.nch_f + J.nch_g);
     std::vector<int32_t> order;
-    if (cfg.launch == PSWEEP_LAUNCH_PERSISTENT) {
+    if (queues) {
         order.assign(kQueueHead, 0);
         for (int q = 0; q < kQueues; ++q) {
             order[q] = (int32_t)(order.size() - kQueueHead);
@@ -632,6 +660,58 @@ const std::vector<int32_t> &item_order(psweep_ctx *ctx, const LevelCam &rc, cons
     return ctx->order_cache.emplace(key, std::move(order)).first->second;
 }
 
+// Workgroups of a kernel that fit on a CU (asked once per kernel).
+int resident_blocks(psweep_ctx *ctx, const KernelEntry *e) {
+    int &n = ctx->resident[e];
+    if (n == 0) {
+        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, e->fn, kWave * e->waves, e->lds);
+        n = std::max(n, 1);
+    }
+    return n;
+}
+
+// Whether a run's sweeps go into one launch over item queues (the persistent
+// kernel), and with which kernel; *tiles: the run's tiles.  A persistent config
+// always does (or the run fails at its launch).  A grid config does where that
+// kernel is built for the run: winner-take-all on 8-bit images, windows 7 and
+// 9, one source count, one tile shape, and neither cost volumes nor per-launch
+// timing asked for, which belong to a launch per job.  The maps are the same,
+// bit for bit, and the levels of a run, or its plane chunks, then fill the chip
+// together (per pass, grids then queues: two levels of 1024x768, 3 sources, 323
+// and 286 us; of 1024x544, 4 sources, 356 and 297 us; one of 1024x768, 762 and
+// 711 us).  One job whose items are all resident at once stays a grid, with no
+// counters at all (320x256, one source: 29.3 against 31.0 us).
+bool one_launch(psweep_ctx *ctx, const psweep_frame *frames, int nf, const psweep_output *out,
+                const KernelEntry **kernel, int64_t *tiles) {
+    const psweep_config &cfg = ctx->cfg;
+    bool fits = cfg.mode == PSWEEP_MODE_WTA && cfg.image_format == PSWEEP_IMAGE_U8 && !ctx->timing;
+    int n_src = 0;
+    *tiles = 0;
+    for (int f = 0; f < nf; ++f) {
+        const int cs = frames[f].camera_set;
+        if (cs < 0 || cs >= (int)ctx->sets.size()) continue;   // refused when the tables are built
+        const CamSet &C = ctx->sets[cs];
+        if (f == 0) n_src = C.n_src;
+        fits = fits && C.n_src == n_src;
+        for (int l = 0; l < cfg.n_levels; ++l) {
+            const psweep_level &L = cfg.level[l];
+            int cw = L.crop_w, ch = L.crop_h;
+            if (l == 1 && C.crop_set) { cw = C.crop[2]; ch = C.crop[3]; }
+            const LevelCam rc = level_cam(C.ref, L.downsample, 0, 0, cw, ch);
+            const int hw = L.window / 2, txo = kWave - 2 * hw, tyo = ctx->tile_rows[l] * ctx->tile_waves[l];
+            *tiles += (int64_t)(std::max(0, rc.w - 2 * hw + txo - 1) / txo) * (std::max(0, rc.h - 2 * hw + tyo - 1) / tyo);
+            fits = fits && (L.window == 7 || L.window == 9) && !out[f].cost_volume[l] &&
+                   ctx->tile_rows[l] == ctx->tile_rows[0] && ctx->tile_waves[l] == ctx->tile_waves[0];
+        }
+    }
+    *kernel = find_kernel(0, ctx->tile_rows[0], ctx->tile_waves[0], n_src, cfg.storage, 0, 1, 0);
+    if (cfg.launch == PSWEEP_LAUNCH_PERSISTENT) return true;
+    if (!fits || !*kernel) return false;
+    const bool one_job = nf * cfg.n_levels == 1;
+    return !one_job || *tiles * std::min(kMaxChunks, std::max(1, ctx->P[0] / 4)) >
+                           (int64_t)ctx->n_cu * resident_blocks(ctx, *kernel);
+}
+
 // Build the per-run tables (host side) for `frames`: job, setup, prep,
 // border and merge records and the jobs' item orders (or, for a persistent
 // launch, the run's item queues), packed at fixed offsets of one blob that is
@@ -648,6 +728,8 @@ psweep_status build_tables(psweep_ctx *ctx, const psweep_frame *frames, int nf, 
     std::vector<MergeDev> merges;
     std::vector<const std::vector<int32_t> *> orders;   // map nodes: stable while the run is built
     if (ctx->order_cache.size() > 192) ctx->order_cache.clear();   // one run adds at most kMaxJobs
+    int64_t run_tiles = 0;
+    blob.queues = one_launch(ctx, frames, nf, out, &blob.kernel, &run_tiles);
     for (int f = 0; f < nf; ++f) {
         const psweep_frame &fr = frames[f];
         const int csi = fr.camera_set;
@@ -748,28 +830,39 @@ psweep_status build_tables(psweep_ctx *ctx, const psweep_frame *frames, int nf, 
             J.tiles_x = rc.w > 2 * hw ? (rc.w - 2 * hw + TXO - 1) / TXO : 0;
             J.tiles_y = rc.h > 2 * hw ? (rc.h - 2 * hw + TYO - 1) / TYO : 0;
             J.rows = rows; J.waves = waves;
-            // plane chunks: enough workgroups for about 28 waves per SIMD
-            // over the launch, so that uneven tiles still balance
+            // plane chunks, where the context sets none.  A grid per job: enough
+            // workgroups for about 28 waves per SIMD, so that uneven tiles still
+            // balance.  One launch over queues: about ten items per CU over the
+            // run, of 4 to 64 planes each.  An item costs about two planes' work
+            // beside its own (set-up, first warp, partial state), and too few or
+            // too long ones leave CUs idle at the end (whole runs: 912 tiles of
+            // 192 planes, 710 us with 3 chunks and 739 with 8; 360 of 94, 265
+            // with 3 and 190 with 8; 7,200 of 256, 15.0 ms with 1 and 12.7 with 4).
             {
                 const int ntile = J.tiles_x * J.tiles_y;
-                int nch = ctx->lay->parts ? ctx->chunks[l] : 1;   // no partial-state room: one pass
-                if (nch == 0) {
+                const int most = ctx->lay->part_chunks;   // under 2: one pass
+                int nch = most < 2 ? 1 : ctx->chunks[l];
+                if (nch == 0 && blob.queues) {
+                    nch = (int)std::min<int64_t>(kMaxChunks, (10LL * ctx->n_cu + run_tiles - 1) / std::max<int64_t>(1, run_tiles));
+                    nch = std::max({1, std::min(nch, P / 4), std::min(kMaxChunks, (P + 63) / 64)});
+                } else if (nch == 0) {
                     const long long target = 28LL * ctx->n_cu * 4;
-                    const long long have = (long long)ntile * waves * (cfg.launch == PSWEEP_LAUNCH_PERSISTENT ? nf : 1);
+                    const long long have = (long long)ntile * waves;
                     nch = have > 0 ? (int)((target + have - 1) / have) : 1;
                     nch = std::max(1, std::min(nch, kMaxChunks));
                 }
                 if (cfg.mode == PSWEEP_MODE_SOFT && nch > 1) nch = std::min(nch, std::max(1, L.n_fronto / 2));
                 J.nch_f = 0; J.nch_g = 0;
+                nch = std::min(nch, std::max(most, 1));
                 if (nch > 1) {
                     const int cs = (P + nch - 1) / nch;
                     J.nch_f = L.n_fronto > 0 ? (L.n_fronto + cs - 1) / cs : 0;
                     J.nch_g = L.n_ground > 0 ? (L.n_ground + cs - 1) / cs : 0;
-                    while (J.nch_f + J.nch_g > kMaxChunks) { if (J.nch_f >= J.nch_g) --J.nch_f; else --J.nch_g; }
+                    while (J.nch_f + J.nch_g > most) { if (J.nch_f >= J.nch_g) --J.nch_f; else --J.nch_g; }
                     if (J.nch_f + J.nch_g <= 1) { J.nch_f = 0; J.nch_g = 0; }
                 }
                 J.part = (float *)(slot + Y.s_part[l]);
-                orders.push_back(&item_order(ctx, rc, L, J));
+                orders.push_back(&item_order(ctx, rc, L, J, blob.queues));
             }
             for (int s = 0; s < C.n_src; ++s) {
                 const LevelCam sc = level_cam(C.src[s], ds, 0, 0, 0, 0);
@@ -859,7 +952,7 @@ psweep_status build_tables(psweep_ctx *ctx, const psweep_frame *frames, int nf, 
     blob.merges = blob.borders + align_up(sizeof(BorderDev) * nj);
     blob.orders = blob.merges + align_up(sizeof(MergeDev) * (nm > 0 ? nm : 1));
     size_t total = blob.orders;
-    const bool queues = cfg.launch == PSWEEP_LAUNCH_PERSISTENT;
+    const bool queues = blob.queues;
     size_t n_items = 0;
     for (int j = 0; j < nj; ++j) {
         if (queues) { n_items += orders[j]->size() - kQueueHead; continue; }
@@ -914,12 +1007,12 @@ psweep_status enqueue(psweep_ctx *ctx, const Blob &blob, char *tb, int which, hi
         // kernel, not by a memset: the run may be captured into a graph)
         if (!do_setup) dsu = nullptr;
         int *counter = (int *)(ctx->base + ctx->lay->off_counter[which]);
-        int n = cfg.launch == PSWEEP_LAUNCH_PERSISTENT ? kQueues * kCounterStride : 0;
+        int n = blob.queues ? kQueues * kCounterStride : 0;
         void *a[] = {&dp, &db, &dsu, &counter, &n};
         PSW_HIP(hipLaunchKernel(psw_prep_kernel(), dim3(256, 1 + maxS, nj), dim3(256), a, 0, stream), "prep");
     }
     if (timed) {
-        const size_t need = cfg.launch == PSWEEP_LAUNCH_PERSISTENT ? 1 : (size_t)nj;
+        const size_t need = blob.queues ? 1 : (size_t)nj;
         while (ctx->ev0.size() < need) {
             hipEvent_t e0, e1;
             PSW_HIP(hipEventCreate(&e0), "event");
@@ -929,7 +1022,7 @@ psweep_status enqueue(psweep_ctx *ctx, const Blob &blob, char *tb, int which, hi
         }
         ctx->n_timed = 0;
     }
-    if (cfg.launch == PSWEEP_LAUNCH_GRID) {
+    if (!blob.queues) {
         std::vector<const KernelEntry *> kern(nj, nullptr);
         int n_launch = 0;
         for (int j = 0; j < nj; ++j) {
@@ -975,18 +1068,10 @@ psweep_status enqueue(psweep_ctx *ctx, const Blob &blob, char *tb, int which, hi
             if (J.rows != ctx->tile_rows[0] || J.waves != ctx->tile_waves[0])
                 return fail(ctx, PSWEEP_EUNSUPPORTED, "persistent launch needs one tile shape");
         }
-        const KernelEntry *e = find_kernel(0, ctx->tile_rows[0], ctx->tile_waves[0], n_src, store, 0, 1, 0);
+        const KernelEntry *e = blob.kernel;
         if (!e) return fail(ctx, PSWEEP_EUNSUPPORTED, "no persistent kernel for this tile/sources/storage");
         int *counter = (int *)(ctx->base + ctx->lay->off_counter[which]);
-        int dev = 0, n_cu = 256;
-        if (hipGetDevice(&dev) == hipSuccess) {
-            hipDeviceProp_t prop;
-            if (hipGetDeviceProperties(&prop, dev) == hipSuccess) n_cu = prop.multiProcessorCount;
-        }
-        int per_cu = 1;
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, e->fn, kWave * ctx->tile_waves[0], e->lds);
-        if (per_cu < 1) per_cu = 1;
-        const int grid = std::min(n_items, n_cu * per_cu);
+        const int grid = std::min(n_items, ctx->n_cu * resident_blocks(ctx, e));
         if (grid > 0) {
             int32_t *queues = (int32_t *)(tb + blob.orders);
             void *a[] = {&dj, &queues, &counter};

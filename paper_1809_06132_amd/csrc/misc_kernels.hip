@@ -376,12 +376,11 @@ __global__ void mask_kernel(MaskDev M) {
 }  // namespace psw
 
 // Scratch of psweep_run_noalloc: job tables, counters, level images,
-// textures and level maps of one run, for callers that cannot allocate.
+// textures, level maps and, as far as they fit, partial states of one run, for callers that cannot allocate.
 // Every GPU the library runs on holds one copy until the process ends; host
 // code uses its device address (from hipGetSymbolAddress, taken once per
 // device with that device current), never the array's name.
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[psw::kStaticScratchBytes];
 
 extern "C" hipError_t psw_static_scratch(void **ptr, size_t *bytes) {
     constexpr int kMaxDevices = 64;
@@ -399,7 +398,7 @@ extern "C" hipError_t psw_static_scratch(void **ptr, size_t *bytes) {
         addr[dev] = p;
     }
     *ptr = addr[dev];
-    *bytes = kStaticScratchBytes;
+    *bytes = psw::kStaticScratchBytes;
     return hipSuccess;
 }
 

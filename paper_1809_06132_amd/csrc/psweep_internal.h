@@ -2,6 +2,7 @@
 // Nothing here is part of the C ABI.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 namespace psw {
@@ -73,6 +74,7 @@ constexpr uint32_t kNoItem = 0xffffffffu;
 constexpr int kCounterStride = 32;
 constexpr int kPartWords = 7;   // c1, kb, c2, cm, cp, first, last (soft: max, sum, sum*theta)
 constexpr int kMaxChunks = 8;
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;   // of psweep_run_noalloc, per GPU
 
 // plane range [kb, ke) of chunk c of a job (chunks never straddle families)
 __host__ __device__ inline void chunk_range(int n_fronto, int n_ground, int nch_f, int nch_g, int c, int *kb,
