@@ -1,6 +1,6 @@
 // Host side of the TSDF map: validation, workspace layout, and the launch
-// sequence of one integration (recentre -> allocate -> initialise new blocks
-// -> count and list visible blocks -> integrate).
+// sequence of one integration (allocate -> count, empty left-behind slots and
+// list visible blocks -> integrate).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -59,7 +59,10 @@ TsdfDev base_dev(const psweep_tsdf *ts) {
     T.block = (float)(8.0 * c.voxel_m);
     T.mu = (float)c.mu_m;
     T.w_max = (float)c.w_max;
-    for (int a = 0; a < 3; ++a) { T.nb[a] = c.blocks[a]; T.b0[a] = ts->b0[a]; }
+    for (int a = 0; a < 3; ++a) {
+        T.nb[a] = c.blocks[a]; T.b0[a] = ts->b0[a];
+        T.w0[a] = ((ts->b0[a] % c.blocks[a]) + c.blocks[a]) % c.blocks[a];
+    }
     T.nslots = ts->nslots;
     T.min_obs = c.min_observations;
     char *w = ts->ws;
@@ -196,14 +199,13 @@ psweep_status psweep_tsdf_integrate(psweep_tsdf *ts, const psweep_camera *cam, c
     T.pitch = pitch ? pitch : cam->width;
     hipStream_t stream = (hipStream_t)hip_stream;
     void *a[] = {&T};
-    const int gs = (ts->nslots + 255) / 256;
     psweep_status st;
-    if ((st = launch(ts, 1, dim3(gs < 4096 ? gs : 4096), dim3(256), a, stream, "tsdf recentre")) != PSWEEP_OK) return st;
-    if ((st = launch(ts, 2, dim3((T.w + 15) / 16, (T.h + 15) / 16), dim3(16, 16), a, stream, "tsdf alloc")) != PSWEEP_OK)
+    if ((st = launch(ts, 1, dim3((T.w + 15) / 16, (T.h + 15) / 16), dim3(16, 16), a, stream, "tsdf alloc")) != PSWEEP_OK)
         return st;
-    if ((st = launch(ts, 3, dim3(ts->nslots), dim3(256), a, stream, "tsdf init")) != PSWEEP_OK) return st;
-    if ((st = launch(ts, 4, dim3(gs), dim3(256), a, stream, "tsdf blocks")) != PSWEEP_OK) return st;
-    if ((st = launch(ts, 5, dim3(ts->nslots), dim3(256), a, stream, "tsdf integrate")) != PSWEEP_OK) return st;
+    const unsigned gb = (unsigned)((ts->nslots + 31ll) / 32);   // 32 slots a workgroup
+    if ((st = launch(ts, 2, dim3(gb), dim3(256), a, stream, "tsdf blocks")) != PSWEEP_OK) return st;
+    const unsigned gi = (unsigned)(ts->nslots < 2048 ? ts->nslots : 2048);
+    if ((st = launch(ts, 3, dim3(gi), dim3(256), a, stream, "tsdf integrate")) != PSWEEP_OK) return st;
     ts->last = T;
     ts->integrated = true;
     return PSWEEP_OK;
@@ -215,9 +217,8 @@ psweep_status psweep_tsdf_extract(psweep_tsdf *ts, float *d_tsdf, float *d_weigh
     if (!ts->integrated) return tfail(ts, PSWEEP_ESTATE, "nothing integrated yet");
     TsdfDev T = ts->last;
     void *a[] = {&T, &d_tsdf, &d_weight, &d_block_count};
-    const long long nvox = (long long)ts->nslots * psw::kBlockVox;
-    const long long g = (nvox + 255) / 256;
-    return launch(ts, 6, dim3(g < 65536 ? (unsigned)g : 65536u), dim3(256), a, (hipStream_t)hip_stream, "tsdf extract");
+    const long long g = ((long long)T.nb[1] * T.nb[2] * 64 + 3) / 4;   // four rows of voxels a workgroup
+    return launch(ts, 4, dim3(g < 65536 ? (unsigned)g : 65536u), dim3(256), a, (hipStream_t)hip_stream, "tsdf extract");
 }
 
 psweep_status psweep_tsdf_region(const psweep_tsdf *ts, int32_t first_block[3]) {
@@ -231,7 +232,7 @@ psweep_status psweep_tsdf_stats(psweep_tsdf *ts, int32_t *d_stats, void *hip_str
     if (!ts->integrated) return tfail(ts, PSWEEP_ESTATE, "nothing integrated yet");
     TsdfDev T = ts->last;
     void *a[] = {&T, &d_stats};
-    return launch(ts, 7, dim3(1), dim3(64), a, (hipStream_t)hip_stream, "tsdf stats");
+    return launch(ts, 5, dim3(1), dim3(1024), a, (hipStream_t)hip_stream, "tsdf stats");
 }
 
 void psweep_tsdf_destroy(psweep_tsdf *ts) {

@@ -18,12 +18,13 @@ struct TsdfDev {
     float R[9], t[3];
     float voxel, block, mu, w_max;
     int32_t b0[3], nb[3];
+    int32_t w0[3];              // b0 mod nb: the first block's place in the slot grid
     int32_t nslots, min_obs;
     const float *depth;
     int64_t pitch;
     unsigned long long *keys;   // packed block coordinates + valid bit, 0 = empty
     int32_t *count, *seen, *fresh, *list;
-    int32_t *counters;          // [0] visible blocks, [1] allocated slots
+    int32_t *counters;          // [0] visible blocks
     float *D, *W;               // [slot][512]
 };
 

@@ -106,3 +106,38 @@ def test_tsdf_reset_and_far_move_empty_the_map():
     tm.integrate(seq.cam, seq.poses[1], (0.0, 0.0, 4.0), torch.full_like(d, float("nan")))
     assert tm.stats()[0] == 0
     tm.close()
+
+
+@pytest.mark.parametrize("blocks,moves", [((5, 3, 9), (0, 3, 1, 0, -2, 0)), ((1, 4, 3), (0, 1, 0)), ((33, 2, 7), (0, 0, 5, 0))],
+                         ids=["there_and_back", "one_block_wide", "odd_row"])
+def test_tsdf_box_that_returns(blocks, moves):
+    """A box that moves away and comes back: blocks that left it are empty
+    when they return, and a block seen but not yet in view stands for no
+    observation (static camera, box moved along z by whole blocks), against
+    the oracle; boxes of one slot row, and of rows past a wave's lanes."""
+    TsdfMap = _gpu()
+    seq = scenegen.depth_sequence(n_frames=1, w=160, h=120, seed=1011)
+    tm = TsdfMap(voxel=VOX, mu=MU, blocks=blocks, min_obs=1, max_width=160, max_height=120)
+    o = oracle.TsdfOracle(VOX, MU, blocks, min_obs=1)
+    d = seq.depths[0]
+    infos = []
+    for m in moves:
+        centre = (0.0, 0.5, 4.0 + 8 * VOX * m)
+        tm.integrate(seq.cam, seq.poses[0], centre, torch.from_numpy(d).cuda())
+        inf = o.integrate(seq.cam, seq.poses[0], d, centre)
+        inf["b0"] = o.b0.copy()
+        infos.append(inf)
+    out = tm.extract()
+    torch.cuda.synchronize()
+    g_d, g_w, g_c = out["tsdf"].cpu().numpy(), out["weight"].cpu().numpy(), out["count"].cpu().numpy()
+    assert np.array_equal(out["first_block"], o.b0)
+    bad_blk, bad_vox = _margin_masks(infos, _pen_tol(blocks))
+    assert np.array_equal(g_c[~bad_blk], o.count[~bad_blk])
+    ok = ~bad_vox
+    assert ok.mean() > 0.9
+    assert np.array_equal(g_w[ok], o.W[ok].astype(np.float32))
+    od = o.extract()
+    assert np.array_equal(np.isfinite(g_d[ok]), np.isfinite(od[ok]))
+    fin = ok & np.isfinite(od)
+    assert fin.sum() > 0 and np.abs(g_d[fin] - od[fin]).max() <= 1e-4
+    tm.close()
