@@ -22,7 +22,7 @@ using namespace psw;
 extern "C" const void *psw_prep_kernel();
 extern "C" const void *psw_merge_kernel();
 extern "C" const void *psw_chunk_merge_kernel();
-extern "C" const void *psw_filter_kernel();
+extern "C" const void *psw_filter_kernel(int win);
 extern "C" const void *psw_mask_kernel();
 extern "C" const void *psw_backward_kernel(int win, int n_src, int img, int image_grads, int ground);
 extern "C" size_t psw_backward_lds(int win, int n_src, int image_grads);
@@ -1373,8 +1373,9 @@ psweep_status psweep_filter(psweep_ctx *ctx, int32_t camera_set, const psweep_ma
     F.out_pitch = out_pitch ? out_pitch : c.width;
     hipStream_t stream = (hipStream_t)hip_stream;
     void *a[] = {&F};
-    PSW_HIP(hipLaunchKernel(psw_filter_kernel(), dim3((c.width + 15) / 16, (c.height + 15) / 16), dim3(16, 16), a, 0,
-                            stream), "filter");
+    // 64 x 16 output pixels a workgroup
+    PSW_HIP(hipLaunchKernel(psw_filter_kernel(prm->window), dim3((c.width + 63) / 64, (c.height + 15) / 16), dim3(256),
+                            a, 0, stream), "filter");
     return PSWEEP_OK;
 }
 
