@@ -37,11 +37,12 @@
 // safety factor of 4 for FP32 rounding).  Below a floor of 1/16 grey^2 per
 // pixel FP32 cancellation in s_bb can exceed the bound, so there (and for a
 // bound that is not finite) every tap goes to the gradient image directly.
-// Before the atomics, the taps neighbouring samples share are folded
-// together in registers: a lane's bottom taps with the same lane's top taps
-// of the next sample row, and a lane's right taps with the left taps of the
-// lane to its right, about one atomic per sample at unit scale instead of
-// four.
+// Every sample sends its four taps there, four atomics at one address and three
+// constant offsets from it (a sample on the image's last row or column has zero
+// weight beyond it).  Folding the taps that neighbouring samples share in
+// registers first leaves one atomic in four, but the kernel is bound by its
+// vector instructions, and the folding took more of them than it saved (640x480,
+// two sources, 64 planes, window 7: 571 us with it, 492 us without).
 //
 // Tile layout: 16 output rows, lane = sample column, 8 waves of 2 output
 // rows.  Per output pixel the channels G/D,
@@ -63,24 +64,23 @@
 
 namespace psw {
 
-// lane l gets v of lane l - 1 (wave_shr:1) or of lane l + 1 (wave_shl:1);
-// the lane with no neighbour gets `fill`
-__device__ __forceinline__ int lane_shr1_i(int v, int fill) {
-    return __builtin_amdgcn_update_dpp(fill, v, 0x138, 0xf, 0xf, false);
-}
-__device__ __forceinline__ int lane_shl1_i(int v, int fill) {
-    return __builtin_amdgcn_update_dpp(fill, v, 0x130, 0xf, 0xf, false);
-}
-
 // atomic add of v to the float at byte offset off of a buffer (no return)
 __device__ __forceinline__ void gadd(__amdgpu_buffer_rsrc_t rs, int off, float v) {
     __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(v, rs, off, 0, 0);
 }
 
-// fixed-point atomic add to a 64-bit sum in LDS (no return): v times the
-// scale, truncated (|v * scale| < 2^61)
-__device__ __forceinline__ void ladd(unsigned long long *p, float v, float scale) {
-    __hip_atomic_fetch_add(p, (unsigned long long)(long long)(v * scale), __ATOMIC_RELAXED,
+// fixed-point atomic add to a 64-bit sum in LDS (no return): x, |x| < 2^61,
+// rounded to an integer.  x = 2^32 h + l with h the nearest integer to x / 2^32
+// and l exact (|l| <= 2^31), so that two 32-bit conversions and the carry of
+// l's sign make the 64-bit integer: 7 instructions, the compiler's own
+// conversion takes 12.  (The conversions as instructions: they saturate.)
+__device__ __forceinline__ void ladd(unsigned long long *p, float x) {
+    const float h = __builtin_rintf(x * 0x1p-32f), l = fmaf(h, -0x1p32f, x);
+    int hi, lo;
+    asm("v_cvt_i32_f32 %0, %1" : "=v"(lo) : "v"(l));
+    asm("v_cvt_i32_f32 %0, %1" : "=v"(hi) : "v"(h));
+    hi += lo >> 31;
+    __hip_atomic_fetch_add(p, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
@@ -455,6 +455,9 @@ struct Backward {
 #pragma unroll
                         for (int s = 0; s < S; ++s) nvalid += c4[s] < __builtin_huge_valf() ? 1 : 0;
                         const int kk = K < nvalid ? K : nvalid;
+                        // dL/dZ of a chosen window, -dC / (2 kk) (without the
+                        // division for the usual kk <= 2; same value)
+                        const float G = K <= 2 ? dC * (kk == 2 ? -0.25f : -0.5f) : -0.5f * dC / (float)kk;
 #pragma unroll
                         for (int s = 0; s < S; ++s) {
                             int rank = 0;
@@ -463,7 +466,6 @@ struct Backward {
                                 rank += (c4[t] < c4[s] || (c4[t] == c4[s] && t < s)) ? 1 : 0;
                             const bool chosen = live && c4[s] < __builtin_huge_valf() && rank < kk &&
                                                 __builtin_fabsf(zs[s]) < 1.0f;
-                            const float G = -0.5f * dC / (float)kk;   // dL/dZ of a chosen window
                             const float invD = isd_a[i] * rsb[s];
                             const float varb_inv = rsb[s] * rsb[s];
                             const float bbar = hbs[s] * invN;
@@ -511,10 +513,6 @@ struct Backward {
                 unsigned long long *pat = patch + (size_t)s * PH * PW;
                 if (GI) { pox = porg[2 * s]; poy = porg[2 * s + 1]; }
                 if (GI && scale == 0.0f) { pox = -(1 << 30); poy = -(1 << 30); }   // every tap direct
-                // patch taps carried down from the previous sample row of this
-                // lane: patch index (-1: none) and value of (v1, i0) and (v1, i1)
-                int ca0 = -1, ca1 = -1;
-                float cv0 = 0.f, cv1 = 0.f;
 #pragma unroll
                 for (int i = 0; i < RS; ++i) {
                     const int j = j0 + i;
@@ -536,10 +534,6 @@ struct Backward {
                     const float sC = wsum<WIN>(rC, sh), sE = wsum<WIN>(rE, sh);
                     const float b = tile[((size_t)s * T + j) * kWave + lane];
                     const float gb = fmaf(aw[i], sA, -sB) + fmaf(-b, sC, sE);
-                    // this sample's patch taps (v0, i0), (v0, i1), (v1, i0), (v1, i1):
-                    // patch index (-1: none) and gradient
-                    int a00 = -1, a10 = -1, a01 = -1, a11 = -1;
-                    float c00 = 0.f, c10 = 0.f, c01 = 0.f, c11 = 0.f;
                     if ((gb != 0.0f) & !is_neg_zero(b)) {
                         // recompute the warp of this sample with its derivatives
                         const float X = fmaf(h3x, tq[i], fmaf(h2x, yw[i], px));
@@ -551,26 +545,28 @@ struct Backward {
                         const float u = fmaf(X * inv, sd.fx, sd.cx);
                         const float v = fmaf(Y * inv, sd.fy, sd.cy);
                         const int i0 = (int)u, v0 = (int)v;
-                        const int i1 = i0 + 1 < sd.w ? i0 + 1 : sd.w - 1;
-                        const int v1 = v0 + 1 < sd.h ? v0 + 1 : sd.h - 1;
-                        const float al = u - (float)i0, be = v - (float)v0;
+                        const float al = __builtin_amdgcn_fractf(u), be = __builtin_amdgcn_fractf(v);
                         float dbu, dbv;
                         Texel<IMG>::slope(rs, __umul24((uint32_t)v0, row_bytes) + (uint32_t)i0 * Texel<IMG>::bytes, al, be,
                                           &dbu, &dbv);
                         if (GI && gimg) {
-                            c00 = gb * (1.0f - al) * (1.0f - be); c10 = gb * al * (1.0f - be);
-                            c01 = gb * (1.0f - al) * be; c11 = gb * al * be;
                             const int pi = i0 - pox, pj = v0 - poy;
                             if ((uint32_t)pi < (uint32_t)(PW - 1) && (uint32_t)pj < (uint32_t)(PH - 1)) {
-                                a00 = pj * PW + pi;
-                                a10 = a00 + (i1 - i0);
-                                a01 = a00 + (v1 - v0) * PW;
-                                a11 = a01 + (i1 - i0);
+                                // the gradient times the patch's scale, a power of two
+                                const float gs = gb * scale, g1 = gs * al, g0 = gs * (1.0f - al);
+                                unsigned long long *const q = pat + pj * PW + pi;
+                                ladd(q, g0 * (1.0f - be));
+                                ladd(q + 1, g1 * (1.0f - be));
+                                ladd(q + PW, g0 * be);
+                                ladd(q + PW + 1, g1 * be);
                             } else {
-                                gadd(grs, (int)(__umul24((uint32_t)v0, grow) + (uint32_t)i0 * 4u), c00);
-                                gadd(grs, (int)(__umul24((uint32_t)v0, grow) + (uint32_t)i1 * 4u), c10);
-                                gadd(grs, (int)(__umul24((uint32_t)v1, grow) + (uint32_t)i0 * 4u), c01);
-                                gadd(grs, (int)(__umul24((uint32_t)v1, grow) + (uint32_t)i1 * 4u), c11);
+                                const int i1 = i0 + 1 < sd.w ? i0 + 1 : sd.w - 1;
+                                const int v1 = v0 + 1 < sd.h ? v0 + 1 : sd.h - 1;
+                                const float g0 = gb * (1.0f - al), g1 = gb * al;
+                                gadd(grs, (int)(__umul24((uint32_t)v0, grow) + (uint32_t)i0 * 4u), g0 * (1.0f - be));
+                                gadd(grs, (int)(__umul24((uint32_t)v0, grow) + (uint32_t)i1 * 4u), g1 * (1.0f - be));
+                                gadd(grs, (int)(__umul24((uint32_t)v1, grow) + (uint32_t)i0 * 4u), g0 * be);
+                                gadd(grs, (int)(__umul24((uint32_t)v1, grow) + (uint32_t)i1 * 4u), g1 * be);
                             }
                         }
                         // (X, Y, Z) = H (x, y, tau) is the source point P divided by
@@ -595,31 +591,6 @@ struct Backward {
                         ps[4] = fmaf(gb, fmaf(Z, e0, -X * e2), ps[4]);
                         ps[5] = fmaf(gb, fmaf(X, e1, -Y * e0), ps[5]);
                     }
-                    if (GI && gimg) {
-                        // (a) this lane's bottom taps of the previous row are this
-                        // row's top taps (same texel row and columns)
-                        if (ca0 >= 0 && ca0 == a00) {
-                            c00 += cv0;
-                            c10 += cv1;   // ca1 is a10, or was handed on (cv1 = 0)
-                        } else {
-                            if (ca0 >= 0) ladd(pat + ca0, cv0, scale);
-                            if (ca1 >= 0) ladd(pat + ca1, cv1, scale);
-                        }
-                        // (b) the left lane's right taps are this lane's left taps;
-                        // the left lane then drops them
-                        const int l10 = lane_shr1_i(a10, -1);
-                        const float l10v = shr1(c10), l11v = shr1(c11);
-                        if (a00 >= 0 && l10 == a00) { c00 += l10v; c01 += l11v; }
-                        const bool handed = a10 >= 0 && lane_shl1_i(a00, -1) == a10;
-                        if (a00 >= 0) ladd(pat + a00, c00, scale);
-                        if (a10 >= 0 && !handed) ladd(pat + a10, c10, scale);
-                        ca0 = a01; cv0 = c01;
-                        ca1 = handed ? -1 : a11; cv1 = handed ? 0.f : c11;
-                    }
-                }
-                if (GI && gimg) {
-                    if (ca0 >= 0) ladd(pat + ca0, cv0, scale);
-                    if (ca1 >= 0) ladd(pat + ca1, cv1, scale);
                 }
 #pragma unroll
                 for (int a = 0; a < 3; ++a) acc[s][a] = fmaf(ps[a], pf, acc[s][a]);
