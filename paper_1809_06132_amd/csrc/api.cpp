@@ -1288,14 +1288,6 @@ psweep_status psweep_soft_depth_backward(psweep_ctx *ctx, const float *d_grad_in
     // source image gradients are optional: a NULL array or entry skips them
     float *gsrc[4] = {nullptr, nullptr, nullptr, nullptr};
     for (int s = 0; s < C.n_src; ++s) gsrc[s] = d_grad_src ? d_grad_src[s] : nullptr;
-    const void *zk = psw_zero_kernel();
-    for (int s = 0; s < C.n_src; ++s) {
-        float *p = gsrc[s];
-        if (!p) continue;
-        int64_t n = (int64_t)C.src[s].width * C.src[s].height;
-        void *a[] = {&p, &n};
-        PSW_HIP(hipLaunchKernel(zk, dim3(256), dim3(256), a, 0, stream), "zero");
-    }
     const int win = ctx->cfg.level[0].window;
     bool any_image = false;
     for (int s = 0; s < C.n_src; ++s) any_image |= gsrc[s] != nullptr;
@@ -1319,15 +1311,21 @@ psweep_status psweep_soft_depth_backward(psweep_ctx *ctx, const float *d_grad_in
     const long long wpg = psw_backward_threads(any_image ? 1 : 0) / kWave;   // waves per workgroup
     int nch = tiles ? (int)((14LL * ctx->n_cu * 4 + wpg * tiles - 1) / (wpg * tiles)) : 1;
     nch = std::max(1, std::min(std::min(nch, 16), std::max(1, nf / 2)));
-    // the pose gradient: one partial row of 6 S doubles per workgroup, in the
+    // the pose gradient: 6 S partial sums per workgroup (doubles), in the
     // plane-chunk region of the soft run (merged by then), summed in order
     double *gpart = reinterpret_cast<double *>(ctx->soft_part);
     const int n_rows = tiles * nch, n_pose = 6 * C.n_src;
     const size_t part_bytes = align_up((size_t)ctx->ref_w[0] * ctx->ref_h[0] * 4 * kPartWords * kMaxChunks);
     if ((size_t)n_rows * n_pose * sizeof(double) > part_bytes)
         return fail(ctx, PSWEEP_EUNSUPPORTED, "backward partial sums exceed the workspace region");
+    float *g0 = gsrc[0], *g1 = gsrc[1], *g2 = gsrc[2], *g3 = gsrc[3];
+    if (any_image) {
+        int64_t n[4] = {0, 0, 0, 0};
+        for (int s = 0; s < C.n_src; ++s) n[s] = (int64_t)C.src[s].width * C.src[s].height;
+        void *a[] = {&g0, &g1, &g2, &g3, &n[0], &n[1], &n[2], &n[3]};
+        PSW_HIP(hipLaunchKernel(psw_zero_kernel(), dim3(256, C.n_src), dim3(256), a, 0, stream), "zero");
+    }
     if (tiles) {
-        float *g0 = gsrc[0], *g1 = gsrc[1], *g2 = gsrc[2], *g3 = gsrc[3];
         const float *rho = ctx->soft_rho, *lse = ctx->soft_lse;
         int64_t sp = ctx->soft_pitch;
         void *a[] = {(void *)&job, (void *)&d_grad_invdepth, (void *)&rho, (void *)&lse, &sp,
@@ -1336,8 +1334,8 @@ psweep_status psweep_soft_depth_backward(psweep_ctx *ctx, const float *d_grad_in
                 "backward");
     }
     {
-        int nr = n_rows, np = n_pose;
-        void *a[] = {&gpart, &nr, &np, &d_grad_pose};
+        int nr = n_rows;
+        void *a[] = {&gpart, &nr, &d_grad_pose};
         PSW_HIP(hipLaunchKernel(psw_pose_reduce_kernel(), dim3(n_pose), dim3(256), a, 0, stream), "pose reduce");
     }
     return PSWEEP_OK;

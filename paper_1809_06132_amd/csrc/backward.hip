@@ -9,27 +9,36 @@
 
 namespace psw {
 
-__global__ void zero_kernel(float *p, int64_t n) {
+// the image gradients of up to four sources, one launch (blockIdx.y: source)
+__global__ void zero_kernel(float *p0, float *p1, float *p2, float *p3, int64_t n0, int64_t n1, int64_t n2, int64_t n3) {
+    float *const p = blockIdx.y == 0 ? p0 : blockIdx.y == 1 ? p1 : blockIdx.y == 2 ? p2 : p3;
+    const int64_t n = blockIdx.y == 0 ? n0 : blockIdx.y == 1 ? n1 : blockIdx.y == 2 ? n2 : n3;
+    if (!p) return;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0.0f;
 }
 
-// Sum of the workgroups' pose partial rows: workgroup c adds column c, each
-// of its 256 threads a strided share of the rows, then a fixed tree (the
-// same order every time).
-__global__ __launch_bounds__(256) void pose_reduce_kernel(const double *__restrict__ gpart, int n_rows, int n,
+// Sum of the workgroups' pose partial sums: workgroup c adds column c, each of
+// its 256 threads a strided share of the rows, then a fixed tree (the same
+// order every time).  Bound by the latency of its reads: four of a thread's are
+// in flight, next to its neighbours' in memory.
+__global__ __launch_bounds__(256) void pose_reduce_kernel(const double *__restrict__ gpart, int n_rows,
                                                           double *__restrict__ gpose) {
-    __shared__ double part[256];
-    const int c = blockIdx.x, t = threadIdx.x;
+    __shared__ double part[256 / kWave];
+    const int t = threadIdx.x;
+    const double *col = gpart + (int64_t)blockIdx.x * n_rows;
     double acc = 0.0;
-    for (int r = t; r < n_rows; r += 256) acc += gpart[(int64_t)r * n + c];
-    part[t] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) part[t] += part[t + w];
-        __syncthreads();
+    for (int r = t; r < n_rows; r += 1024) {
+        double v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = r + 256 * k < n_rows ? col[r + 256 * k] : 0.0;
+        acc += (v[0] + v[1]) + (v[2] + v[3]);
     }
-    if (t == 0) gpose[c] = part[0];
+#pragma unroll
+    for (int o = kWave / 2; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, kWave);
+    if (t % kWave == 0) part[t / kWave] = acc;
+    __syncthreads();
+    if (t == 0) gpose[blockIdx.x] = (part[0] + part[1]) + (part[2] + part[3]);
 }
 
 }  // namespace psw

@@ -84,11 +84,22 @@ __device__ __forceinline__ void ladd(unsigned long long *p, float x) {
                            __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// minimum over the wave
+// v of another lane by DPP (ctrl, rows); lanes without one keep v
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_keep(float v) {
+    const int i = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xf, false));
+}
+// minimum over the wave (uniform): within rows of 16 lanes by shifts of 1, 2, 4
+// and 8, then across rows by broadcasts of their last lanes; no LDS round trips
 __device__ __forceinline__ float wave_min(float v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fminf(v, __shfl_xor(v, o, kWave));
-    return v;
+    v = fminf(v, dpp_keep<0x111, 0xf>(v));
+    v = fminf(v, dpp_keep<0x112, 0xf>(v));
+    v = fminf(v, dpp_keep<0x114, 0xf>(v));
+    v = fminf(v, dpp_keep<0x118, 0xf>(v));
+    v = fminf(v, dpp_keep<0x142, 0xa>(v));
+    v = fminf(v, dpp_keep<0x143, 0xc>(v));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1));
 }
 
 // GI: whether any source's image gradient is wanted (false: pose only).
@@ -622,26 +633,30 @@ struct Backward {
                 }
             }
         }
-        // ---- pose gradient: wave reduction, then the workgroup's partial sum
-        // (one row of gpart per workgroup; a second kernel adds the rows in a
-        // fixed order).  The LDS tile is free: the plane loop ended on a barrier.
-        double *red = reinterpret_cast<double *>(smem);   // [wave][6 S]
+        // ---- pose gradient: the workgroup's partial sum in FP64, a column of
+        // gpart per workgroup (a second kernel adds the workgroups in a fixed
+        // order).  Every lane's 6 S values go to LDS (the tile and channels are
+        // free: the plane loop ended on a barrier), then 16 lanes add up each
+        // value's, 32 in turn and the 16 by lane shuffles: 41 steps for all of
+        // them, where shuffling every value over every wave takes 6 S times 6.
+        float *red = reinterpret_cast<float *>(smem);   // [6 S][kRed]
+        constexpr int kRed = NW * kWave + 16;           // rows half of the banks apart
+        static_assert((size_t)6 * S * kRed * 4 <= lds_tile() + (size_t)(NCH * S + 1) * TYO * kWave * 4, "");
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int a = 0; a < 6; ++a) {
-                double v = (double)acc[s][a];
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
-                if (lane == 0) red[wave * 6 * S + s * 6 + a] = v;
-            }
+            for (int a = 0; a < 6; ++a) red[(s * 6 + a) * kRed + threadIdx.x] = acc[s][a];
         __syncthreads();
-        if (wave == 0 && lane < 6 * S) {
+        const int val = threadIdx.x >> 4, g = threadIdx.x & 15;
+        if (val < 6 * S) {
             double t = 0.0;
+#pragma unroll 8
+            for (int r = 0; r < NW * kWave / 16; ++r) t += (double)red[val * kRed + r * 16 + g];
 #pragma unroll
-            for (int w = 0; w < NW; ++w) t += red[w * 6 * S + lane];
+            for (int o = 8; o >= 1; o >>= 1) t += __shfl_xor(t, o, kWave);
+            const int64_t n_wg = (int64_t)gridDim.x * gridDim.y * gridDim.z;
             const int64_t wg = (int64_t)blockIdx.x + (int64_t)gridDim.x * (blockIdx.y + (int64_t)gridDim.y * blockIdx.z);
-            gpart[wg * 6 * S + lane] = t;
+            if (g == 0) gpart[(int64_t)val * n_wg + wg] = t;
         }
     }
 };
