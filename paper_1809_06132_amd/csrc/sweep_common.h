@@ -30,6 +30,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "psweep_internal.h"
 
 namespace psw {
@@ -74,6 +76,25 @@ template <> struct Stage<2> {
     }
     static __device__ __forceinline__ T bad() { return (uint16_t)0x8000u; }
     static __device__ __forceinline__ float get(T v) { return __uint_as_float(((uint32_t)v) << 16); }
+};
+
+// 16-bit staging held in 32-bit words: every sample rounded to 16 bits as
+// above, but kept as the float it rounds to.  The row loop, which reads every
+// sample about four times, then converts nothing, and up to three sources' FP32
+// tiles still leave four workgroups to a CU: 1024x768, three sources, FP16,
+// 813 -> 713 us a pass (two levels 328 -> 285; two sources, BF16, 265 -> 259).
+// Four sources' FP32 tiles leave three, and there the 16-bit words stay (16
+// frames in FP16 12.8 ms, 13.3 ms wide).
+template <int STORE> struct StageWide : Stage<0> {};
+template <> struct StageWide<1> : Stage<0> {
+    static __device__ __forceinline__ float put(float v) { return (float)(_Float16)v + 0.0f; }
+};
+template <> struct StageWide<2> : Stage<0> {
+    static __device__ __forceinline__ float put(float v) {
+        uint32_t u = __float_as_uint(v);
+        u += 0x7fffu + ((u >> 16) & 1u);
+        return __uint_as_float(u & 0xffff0000u);
+    }
 };
 
 #define PSW_GLOBAL __attribute__((address_space(1)))
@@ -412,16 +433,17 @@ struct Tile {
     static constexpr int NWR = (T + NW - 1) / NW;    // warp rows per wave
     // rows whose texel loads the warp issues together: all of them where the
     // registers they hold (two per load in flight) keep the occupancy that
-    // LDS allows (three or four sources, 8-bit images, FP32 staging, windows
-    // up to 9), else two
-    static constexpr int LG = (IMG == 0 && STORE == 0 && S >= 3 && R == 4 && WIN <= 9) ? NWR : 2;
+    // LDS allows (three sources, or four with FP32 staging; 8-bit images,
+    // windows up to 9), else two
+    static constexpr int LG = (IMG == 0 && (STORE == 0 || S <= 3) && S >= 3 && R == 4 && WIN <= 9) ? NWR : 2;
     // texel loads by index into a texel-strided resource (no address shift,
     // one instruction per sample less), except for the one tile that it takes
     // past 128 VGPRs (two sources, window 9, 8-bit images, FP32 staging on the
     // default tile: 129, i.e. three waves per SIMD), which keeps byte offsets
     static constexpr bool kIndexed = !(IMG == 0 && STORE == 0 && S == 2 && WIN == 9 && R == 4 && NW == 4);
     static constexpr int VR = R + 2 * HW;            // rows each wave runs down
-    using St = Stage<STORE>;
+    static constexpr bool kWide = S <= 3;   // see StageWide
+    using St = typename std::conditional<kWide, StageWide<STORE>, Stage<STORE>>::type;
     using ST = typename St::T;
 
     static constexpr size_t lds_bytes() { return 2 * (size_t)S * T * kWave * sizeof(ST); }
@@ -921,11 +943,10 @@ __global__ __launch_bounds__(kWave *NW) void sweep_persistent_kernel(const JobDe
         // (lane-shift addresses and the like) out of this loop, where they stay
         // live across it: about 17 VGPRs more than either sweep needs.  An
         // opaque lane index in each branch prevents that.  It is used where it
-        // brings the kernel to 4 waves per SIMD (three sources FP32: 129 -> 125
-        // VGPRs; four sources FP16: 145 -> 128, BF16: 144 -> 126).  Elsewhere
-        // it gains no wave, and for four sources FP32 (146 -> 129, still 3
-        // waves) the batch ran 25 % slower with it.
-        constexpr bool opaque = (S == 3 && STORE == 0) || (S == 4 && STORE != 0);
+        // keeps the kernel at 4 waves per SIMD (up to three sources; four with
+        // 16-bit staging: 145 -> 128 VGPRs).  For four sources FP32 (146 -> 129,
+        // still 3 waves) the batch ran 25 % slower with it.
+        constexpr bool opaque = S <= 3 || STORE != 0;
         const bool k2 = S >= 2 && J->best_k == 2;
         if (J->window == 7) {
             if (k2) Tile<7, R, NW, S, STORE, false, 0, true>::run(J, tx, ty, chunk, smem, opaque ? opaque_lane() : lane_id());
