@@ -580,8 +580,7 @@ namespace {
 // start first and short ones fill its end), the size of an item being its
 // (pixel, plane) pairs that meet their plane (the pixels of its tile whose
 // Eq. (1) ray meets the chunk's family, times the chunk's planes; FP64 on the
-// host, from every fourth row and column: a size decides the order and nothing
-// else); ties keep the chunk-major order.  Workgroup b runs on XCD b mod 8 and
+// host); ties keep the chunk-major order.  Workgroup b runs on XCD b mod 8 and
 // takes the next item of that XCD, or the next of the XCD with the most left
 // once its own are dealt.  A fixed order, because each of the queues' counters
 // that the workgroups used to take their items from cost a round trip at every
@@ -618,17 +617,26 @@ const std::vector<int32_t> &item_order(psweep_ctx *ctx, const LevelCam &rc, cons
     }
     const int hw = L.window / 2, txo = kWave - 2 * hw, tyo = J.rows * J.waves;
     std::vector<int64_t> met_f(ntile, 0), met_g(ntile, 0);
-    for (int j = hw; j < rc.h - hw; j += 4) {
+    // Eq. (1)'s ray has z = eta - xi > 0 where xi^2 (x^2 + y^2) < 1, and n . r
+    // is eta (n0 x + n1 y) + n2 z
+    const double *gn = cfg.ground_n;
+    for (int j = hw; j < rc.h - hw; ++j) {
         const double y = (j - rc.cy) / rc.fy;
         const int trow = ((j - hw) / tyo) * J.tiles_x;
-        for (int i = hw; i < rc.w - hw; i += 4) {
-            const double x = (i - rc.cx) / rc.fx;
-            const double q = x * x + y * y;
-            const double eta = (rc.xi + std::sqrt(1.0 + (1.0 - rc.xi * rc.xi) * q)) / (q + 1.0);
-            const double rz = eta - rc.xi;
-            const int t = trow + (i - hw) / txo;
-            met_f[t] += rz > 0.0;
-            met_g[t] += cfg.ground_n[0] * eta * x + cfg.ground_n[1] * eta * y + cfg.ground_n[2] * rz > 0.0;
+        for (int tx = 0; tx < J.tiles_x; ++tx) {
+            int nf = 0, ng = 0;
+            for (int i = hw + tx * txo; i < std::min(hw + (tx + 1) * txo, rc.w - hw); ++i) {
+                const double x = (i - rc.cx) / rc.fx, q = x * x + y * y;
+                nf += rc.xi * rc.xi * q < 1.0;
+                if (gn[2] == 0.0) {
+                    ng += gn[0] * x + gn[1] * y > 0.0;
+                } else {
+                    const double eta = (rc.xi + std::sqrt(1.0 + (1.0 - rc.xi * rc.xi) * q)) / (q + 1.0);
+                    ng += eta * (gn[0] * x + gn[1] * y) + gn[2] * (eta - rc.xi) > 0.0;
+                }
+            }
+            met_f[trow + tx] += nf;
+            met_g[trow + tx] += ng;
         }
     }
     std::vector<int64_t> weight((size_t)nch * ntile);
@@ -710,6 +718,39 @@ bool one_launch(psweep_ctx *ctx, const psweep_frame *frames, int nf, const pswee
     const bool one_job = nf * cfg.n_levels == 1;
     return !one_job || *tiles * std::min(kMaxChunks, std::max(1, ctx->P[0] / 4)) >
                            (int64_t)ctx->n_cu * resident_blocks(ctx, *kernel);
+}
+
+// How many chunks the planes of a level are cut into (automatic count): of at
+// least 4 planes each.  An item costs about three of its (plane, source) steps
+// beside its own work (set-up, first warp, partial state), so that few long
+// items are the least work, but too few leave CUs idle at the end of a launch.
+//
+// Item queues: about sqrt(P S n_cu / (3 tiles)) chunks balance the two (whole
+// runs: 360 tiles of 94 planes, 3 sources, 265 us with 3 chunks and 190 with 8;
+// 748 tiles of 80 planes, 1 source, 132 us with 4 and 154 with 8; 667 of 141, 4
+// sources, 905 with 4 and 813 with 8).  Past 24 items a CU the end of the launch
+// no longer shows: ten a CU, of at most 64 planes (912 tiles of 192 planes,
+// 710 us with 3 chunks and 739 with 8; 7,200 of 256, 15.0 ms with 1, 12.7 with 4).
+//
+// A grid per job, largest items first: sqrt(P S n_cu / (2 tiles)), 4 to 8 (748
+// tiles of 80 planes, 1 source, window 5: 120 us with 4, 125 with 6, 150 with 8;
+// 434 of 60, 2 sources, window 13: 155 with 6, 170 with 4; 240 of 64, 2 sources,
+// window 11: 122 with 8, 128 with 6), but one round of workgroups, four to a CU,
+// instead of a little over one (153 tiles of 149 planes: 199 us with 6, 223 with 8).
+int plane_chunks(const psweep_ctx *ctx, int64_t tiles, int P, int S, bool queues) {
+    const int most = std::max(1, std::min(kMaxChunks, P / 4));
+    if (tiles <= 0) return 1;
+    const double work = (double)P * S * ctx->n_cu / tiles;
+    int64_t nch;
+    if (queues) {
+        nch = std::min<int64_t>(most, std::lround(std::sqrt(work / 3.0)));
+        if (tiles * nch > 24LL * ctx->n_cu) nch = std::max<int64_t>((10LL * ctx->n_cu + tiles - 1) / tiles, (P + 63) / 64);
+    } else {
+        nch = std::max<int64_t>(4, std::min<int64_t>(most, (int64_t)std::ceil(std::sqrt(work / 2.0))));
+        const int64_t round = 4LL * ctx->n_cu;
+        if (tiles * nch > round && tiles * nch <= round + round / 4) nch = round / tiles;
+    }
+    return (int)std::max<int64_t>(1, std::min<int64_t>(nch, most));
 }
 
 // Build the per-run tables (host side) for `frames`: job, setup, prep,
@@ -830,21 +871,15 @@ psweep_status build_tables(psweep_ctx *ctx, const psweep_frame *frames, int nf, 
             J.tiles_x = rc.w > 2 * hw ? (rc.w - 2 * hw + TXO - 1) / TXO : 0;
             J.tiles_y = rc.h > 2 * hw ? (rc.h - 2 * hw + TYO - 1) / TYO : 0;
             J.rows = rows; J.waves = waves;
-            // plane chunks, where the context sets none.  A grid per job: enough
-            // workgroups for about 28 waves per SIMD, so that uneven tiles still
-            // balance.  One launch over queues: about ten items per CU over the
-            // run, of 4 to 64 planes each.  An item costs about two planes' work
-            // beside its own (set-up, first warp, partial state), and too few or
-            // too long ones leave CUs idle at the end (whole runs: 912 tiles of
-            // 192 planes, 710 us with 3 chunks and 739 with 8; 360 of 94, 265
-            // with 3 and 190 with 8; 7,200 of 256, 15.0 ms with 1 and 12.7 with 4).
+            // plane chunks, where the context sets none (see plane_chunks).  Soft
+            // mode: enough workgroups for about 28 waves per SIMD (its outputs
+            // depend on the number, since the chunks' merge rounds).
             {
                 const int ntile = J.tiles_x * J.tiles_y;
                 const int most = ctx->lay->part_chunks;   // under 2: one pass
                 int nch = most < 2 ? 1 : ctx->chunks[l];
-                if (nch == 0 && blob.queues) {
-                    nch = (int)std::min<int64_t>(kMaxChunks, (10LL * ctx->n_cu + run_tiles - 1) / std::max<int64_t>(1, run_tiles));
-                    nch = std::max({1, std::min(nch, P / 4), std::min(kMaxChunks, (P + 63) / 64)});
+                if (nch == 0 && cfg.mode != PSWEEP_MODE_SOFT) {
+                    nch = plane_chunks(ctx, blob.queues ? run_tiles : ntile, P, C.n_src, blob.queues);
                 } else if (nch == 0) {
                     const long long target = 28LL * ctx->n_cu * 4;
                     const long long have = (long long)ntile * waves;
