@@ -37,12 +37,17 @@
 // safety factor of 4 for FP32 rounding).  Below a floor of 1/16 grey^2 per
 // pixel FP32 cancellation in s_bb can exceed the bound, so there (and for a
 // bound that is not finite) every tap goes to the gradient image directly.
-// Every sample sends its four taps there, four atomics at one address and three
-// constant offsets from it (a sample on the image's last row or column has zero
-// weight beyond it).  Folding the taps that neighbouring samples share in
-// registers first leaves one atomic in four, but the kernel is bound by its
-// vector instructions, and the folding took more of them than it saved (640x480,
-// two sources, 64 planes, window 7: 571 us with it, 492 us without).
+// On a level of fronto planes every sample sends its four taps there, four
+// atomics at one address and three constant offsets from it (a sample on the
+// image's last row or column has zero weight beyond it).  Folding the taps that
+// neighbouring samples share in registers first leaves one atomic in four, but
+// the kernel is bound by its vector instructions, and the folding took more of
+// them than it saved (640x480, two sources, 64 planes, window 7: 571 us with it,
+// 492 us without).  On a level with ground planes the taps are folded (a lane's
+// bottom taps with its top taps of the next sample row, its right taps with the
+// left taps of the lane to its right): theta has no bound near the horizon, the
+// scale is coarse for it (a conversion's error reaches 1e-5 of a gradient image,
+// on fronto planes it is below 1e-7), and each conversion counts.
 //
 // Tile layout: 16 output rows, lane = sample column, 8 waves of 2 output
 // rows.  Per output pixel the channels G/D,
@@ -69,8 +74,8 @@ __device__ __forceinline__ void gadd(__amdgpu_buffer_rsrc_t rs, int off, float v
     __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(v, rs, off, 0, 0);
 }
 
-// fixed-point atomic add to a 64-bit sum in LDS (no return): x, |x| < 2^61,
-// rounded to an integer.  x = 2^32 h + l with h the nearest integer to x / 2^32
+// fixed-point atomic add to a 64-bit sum in LDS (no return): x, |x| < 2^61, its
+// fraction dropped.  x = 2^32 h + l with h the nearest integer to x / 2^32
 // and l exact (|l| <= 2^31), so that two 32-bit conversions and the carry of
 // l's sign make the 64-bit integer: 7 instructions, the compiler's own
 // conversion takes 12.  (The conversions as instructions: they saturate.)
@@ -82,6 +87,14 @@ __device__ __forceinline__ void ladd(unsigned long long *p, float x) {
     hi += lo >> 31;
     __hip_atomic_fetch_add(p, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// int of the lane to the left / right; lane 0 / 63 gets fill
+__device__ __forceinline__ int lane_shr1_i(int v, int fill) {
+    return __builtin_amdgcn_update_dpp(fill, v, 0x138, 0xf, 0xf, false);
+}
+__device__ __forceinline__ int lane_shl1_i(int v, int fill) {
+    return __builtin_amdgcn_update_dpp(fill, v, 0x130, 0xf, 0xf, false);
 }
 
 // v of another lane by DPP (ctrl, rows); lanes without one keep v
@@ -524,6 +537,10 @@ struct Backward {
                 unsigned long long *pat = patch + (size_t)s * PH * PW;
                 if (GI) { pox = porg[2 * s]; poy = porg[2 * s + 1]; }
                 if (GI && scale == 0.0f) { pox = -(1 << 30); poy = -(1 << 30); }   // every tap direct
+                // (folded taps) carried down from the previous sample row of this
+                // lane: patch index (-1: none) and value of (v1, i0) and (v1, i1)
+                int ca0 = -1, ca1 = -1;
+                float cv0 = 0.f, cv1 = 0.f;
 #pragma unroll
                 for (int i = 0; i < RS; ++i) {
                     const int j = j0 + i;
@@ -545,6 +562,10 @@ struct Backward {
                     const float sC = wsum<WIN>(rC, sh), sE = wsum<WIN>(rE, sh);
                     const float b = tile[((size_t)s * T + j) * kWave + lane];
                     const float gb = fmaf(aw[i], sA, -sB) + fmaf(-b, sC, sE);
+                    // (folded taps) this sample's (v0, i0), (v0, i1), (v1, i0) and
+                    // (v1, i1): patch index (-1: none) and scaled gradient
+                    int a00 = -1, a10 = -1, a01 = -1, a11 = -1;
+                    float c00 = 0.f, c10 = 0.f, c01 = 0.f, c11 = 0.f;
                     if ((gb != 0.0f) & !is_neg_zero(b)) {
                         // recompute the warp of this sample with its derivatives
                         const float X = fmaf(h3x, tq[i], fmaf(h2x, yw[i], px));
@@ -565,11 +586,18 @@ struct Backward {
                             if ((uint32_t)pi < (uint32_t)(PW - 1) && (uint32_t)pj < (uint32_t)(PH - 1)) {
                                 // the gradient times the patch's scale, a power of two
                                 const float gs = gb * scale, g1 = gs * al, g0 = gs * (1.0f - al);
-                                unsigned long long *const q = pat + pj * PW + pi;
-                                ladd(q, g0 * (1.0f - be));
-                                ladd(q + 1, g1 * (1.0f - be));
-                                ladd(q + PW, g0 * be);
-                                ladd(q + PW + 1, g1 * be);
+                                if constexpr (GND) {
+                                    a00 = pj * PW + pi; a10 = a00 + 1;
+                                    a01 = a00 + PW; a11 = a01 + 1;
+                                    c00 = g0 * (1.0f - be); c10 = g1 * (1.0f - be);
+                                    c01 = g0 * be; c11 = g1 * be;
+                                } else {
+                                    unsigned long long *const q = pat + pj * PW + pi;
+                                    ladd(q, g0 * (1.0f - be));
+                                    ladd(q + 1, g1 * (1.0f - be));
+                                    ladd(q + PW, g0 * be);
+                                    ladd(q + PW + 1, g1 * be);
+                                }
                             } else {
                                 const int i1 = i0 + 1 < sd.w ? i0 + 1 : sd.w - 1;
                                 const int v1 = v0 + 1 < sd.h ? v0 + 1 : sd.h - 1;
@@ -602,6 +630,33 @@ struct Backward {
                         ps[4] = fmaf(gb, fmaf(Z, e0, -X * e2), ps[4]);
                         ps[5] = fmaf(gb, fmaf(X, e1, -Y * e0), ps[5]);
                     }
+                    if constexpr (GI && GND) {
+                        if (gimg) {
+                            // (a) this lane's bottom taps of the previous row are this
+                            // row's top taps (same texel row and columns)
+                            if (ca0 >= 0 && ca0 == a00) {
+                                c00 += cv0;
+                                c10 += cv1;   // ca1 is a10, or was handed on (cv1 = 0)
+                            } else {
+                                if (ca0 >= 0) ladd(pat + ca0, cv0);
+                                if (ca1 >= 0) ladd(pat + ca1, cv1);
+                            }
+                            // (b) the left lane's right taps are this lane's left taps;
+                            // the left lane then drops them
+                            const int l10 = lane_shr1_i(a10, -1);
+                            const float l10v = shr1(c10), l11v = shr1(c11);
+                            if (a00 >= 0 && l10 == a00) { c00 += l10v; c01 += l11v; }
+                            const bool handed = a10 >= 0 && lane_shl1_i(a00, -1) == a10;
+                            if (a00 >= 0) ladd(pat + a00, c00);
+                            if (a10 >= 0 && !handed) ladd(pat + a10, c10);
+                            ca0 = a01; cv0 = c01;
+                            ca1 = handed ? -1 : a11; cv1 = handed ? 0.f : c11;
+                        }
+                    }
+                }
+                if constexpr (GI && GND) {
+                    if (ca0 >= 0) ladd(pat + ca0, cv0);
+                    if (ca1 >= 0) ladd(pat + ca1, cv1);
                 }
 #pragma unroll
                 for (int a = 0; a < 3; ++a) acc[s][a] = fmaf(ps[a], pf, acc[s][a]);
