@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <numeric>
 #include <new>
 #include <string>
 #include <vector>
@@ -571,21 +572,27 @@ psweep_status psweep_plane_pixels_met(const psweep_ctx *ctx, const psweep_frame 
 
 namespace {
 
+constexpr int kDealGroup = 256;   // see item_order: an item for each CU
+
 // The items of one job, dealt out over the XCDs: tile row y goes to XCD y mod 8,
 // so that an XCD's L2 holds the source texels of its rows.  Depends only on the
 // level's geometry and the launch shape: cached.
 //
-// Grid launch: the item of every workgroup (see JobDev::order).  Each XCD's
-// items are sorted largest first, which shortens the launch's tail (long items
-// start first and short ones fill its end), the size of an item being its
-// (pixel, plane) pairs that meet their plane (the pixels of its tile whose
-// Eq. (1) ray meets the chunk's family, times the chunk's planes; FP64 on the
-// host); ties keep the chunk-major order.  Workgroup b runs on XCD b mod 8 and
-// takes the next item of that XCD, or the next of the XCD with the most left
-// once its own are dealt.  A fixed order, because each of the queues' counters
-// that the workgroups used to take their items from cost a round trip at every
-// workgroup's start and served them one at a time (320x256, one source, 768
-// workgroups: the sweep took 27 us, and 19 us dealt).
+// Grid launch: the item of every workgroup (see JobDev::order), largest first,
+// which shortens the launch's tail (long items start first and short ones fill
+// its end), the size of an item being its (pixel, plane) pairs that meet their
+// plane (the pixels of its tile whose Eq. (1) ray meets the chunk's family,
+// times the chunk's planes; FP64 on the host); ties keep the chunk-major order.
+// Workgroup b runs on XCD b mod 8, so that every XCD gets as many items as any
+// other, and tile rows differ in size: of each kDealGroup items of the order an
+// XCD gets an eighth, those of its own rows first, and every XCD has the same
+// work (487x275 float images, 17 tile rows, 149 planes, 3 sources: 224 us with
+// each XCD's own rows until they run out, 175 us; 320x256: 29.7 and 28.2 us;
+// groups of 64 or 1024 items the same within 3 us, or slower).  A fixed order,
+// because each of the queues' counters that the workgroups used to take their
+// items from cost a round trip at every workgroup's start and served them one
+// at a time (320x256, one source, 768 workgroups: the sweep took 27 us, and 19
+// us dealt).
 //
 // Persistent launch: the eight XCDs' queues one after another, behind their
 // nine starts, each row by row, every chunk of a tile row before the next row,
@@ -647,24 +654,28 @@ const std::vector<int32_t> &item_order(psweep_ctx *ctx, const LevelCam &rc, cons
         const int64_t pg = std::max(0, ke - std::max(kb, L.n_fronto));
         for (int t = 0; t < ntile; ++t) weight[(size_t)c * ntile + t] = met_f[t] * pf + met_g[t] * pg;
     }
-    std::vector<int32_t> share[kQueues];
-    for (int q = 0; q < kQueues; ++q) {
-        for (int c = 0; c < nch; ++c)
-            for (int y = q; y < J.tiles_y; y += kQueues)
-                for (int x = 0; x < J.tiles_x; ++x) share[q].push_back(c * ntile + y * J.tiles_x + x);
-        std::stable_sort(share[q].begin(), share[q].end(),
-                         [&](int32_t a, int32_t b) { return weight[a] > weight[b]; });
+    const int n = ntile * nch;
+    std::vector<int32_t> sorted(n), spill, share[kQueues];
+    std::iota(sorted.begin(), sorted.end(), 0);
+    std::stable_sort(sorted.begin(), sorted.end(), [&](int32_t a, int32_t b) { return weight[a] > weight[b]; });
+    for (int g = 0; g < n; g += kDealGroup) {
+        const int m = std::min(n - g, kDealGroup);
+        int room[kQueues];
+        for (int q = 0; q < kQueues; ++q) room[q] = (m - q + kQueues - 1) / kQueues;
+        spill.clear();
+        for (int i = g; i < g + m; ++i) {
+            const int q = sorted[i] % ntile / J.tiles_x % kQueues;
+            if (room[q] > 0) { --room[q]; share[q].push_back(sorted[i]); }
+            else spill.push_back(sorted[i]);
+        }
+        for (const int32_t it : spill) {
+            const int q = (int)(std::max_element(room, room + kQueues) - room);
+            --room[q];
+            share[q].push_back(it);
+        }
     }
-    size_t at[kQueues] = {};
-    const size_t n = (size_t)ntile * nch;
-    order.reserve(n);
-    while (order.size() < n) {
-        int q = (int)(order.size() % kQueues);
-        if (at[q] == share[q].size())
-            for (int o = 0; o < kQueues; ++o)
-                if (share[o].size() - at[o] > share[q].size() - at[q]) q = o;
-        order.push_back(share[q][at[q]++]);
-    }
+    order.resize(n);
+    for (int i = 0; i < n; ++i) order[i] = share[i % kQueues][i / kQueues];
     return ctx->order_cache.emplace(key, std::move(order)).first->second;
 }
 
@@ -735,8 +746,7 @@ bool one_launch(psweep_ctx *ctx, const psweep_frame *frames, int nf, const pswee
 // A grid per job, largest items first: sqrt(P S n_cu / (2 tiles)), 4 to 8 (748
 // tiles of 80 planes, 1 source, window 5: 120 us with 4, 125 with 6, 150 with 8;
 // 434 of 60, 2 sources, window 13: 155 with 6, 170 with 4; 240 of 64, 2 sources,
-// window 11: 122 with 8, 128 with 6), but one round of workgroups, four to a CU,
-// instead of a little over one (153 tiles of 149 planes: 199 us with 6, 223 with 8).
+// window 11: 115 with 8, 123 with 6; 153 of 149, 3 sources: 175 with 8, 189 with 6).
 int plane_chunks(const psweep_ctx *ctx, int64_t tiles, int P, int S, bool queues) {
     const int most = std::max(1, std::min(kMaxChunks, P / 4));
     if (tiles <= 0) return 1;
@@ -747,8 +757,6 @@ int plane_chunks(const psweep_ctx *ctx, int64_t tiles, int P, int S, bool queues
         if (tiles * nch > 24LL * ctx->n_cu) nch = std::max<int64_t>((10LL * ctx->n_cu + tiles - 1) / tiles, (P + 63) / 64);
     } else {
         nch = std::max<int64_t>(4, std::min<int64_t>(most, (int64_t)std::ceil(std::sqrt(work / 2.0))));
-        const int64_t round = 4LL * ctx->n_cu;
-        if (tiles * nch > round && tiles * nch <= round + round / 4) nch = round / tiles;
     }
     return (int)std::max<int64_t>(1, std::min<int64_t>(nch, most));
 }
