@@ -28,8 +28,8 @@ from .sweep import PlaneSweep
 def perturb_pose(R: np.ndarray, t: np.ndarray, xi: np.ndarray):
     """exp(xi) * T with xi = (v, omega): R' = Exp(omega) R, t' = Exp(omega) t + v
     (first order: X_s + v + omega x X_s), computed by the library."""
-    Ro, to = P.psweep_perturb_pose(np.asarray(R, np.float64).ravel(), np.asarray(t, np.float64).ravel(),
-                                   np.asarray(xi, np.float64).ravel())
+    Ro, to = P.psweep_perturb_pose(np.asarray(R, np.float64).ravel().tolist(), np.asarray(t, np.float64).ravel().tolist(),
+                                   np.asarray(xi, np.float64).ravel().tolist())
     return np.asarray(Ro).reshape(3, 3), np.asarray(to)
 
 
@@ -41,17 +41,21 @@ class _Pose:
 class SoftDepth(torch.autograd.Function):
     @staticmethod
     def forward(ctx, sweep: PlaneSweep, ref: torch.Tensor, pose_xi: torch.Tensor, *srcs: torch.Tensor):
+        # the GPU waits for this thread here: its own work goes first (the images'
+        # conversion), and the pose arithmetic beside it
+        if sweep.image_dtype == torch.float32:
+            u8 = [s.detach().float().contiguous() for s in srcs]
+            ref = ref.detach().float().contiguous()
+        else:
+            u8 = [s if s.dtype == torch.uint8 else s.detach().round().clamp_(0, 255).to(torch.uint8) for s in srcs]
         ref_cam, src_cams = sweep.cams[0]
         base = sweep.base_poses
         xi = pose_xi.detach().to("cpu", torch.float64).numpy()
         poses = [_Pose(*perturb_pose(np.asarray(p.R), np.asarray(p.t), xi[s])) for s, p in enumerate(base)]
         sweep.set_cameras(0, ref_cam, src_cams, poses)
-        if sweep.image_dtype == torch.float32:
-            u8 = [s.detach().float().contiguous() for s in srcs]
-            ref = ref.detach().float().contiguous()
-        else:
-            u8 = [s if s.dtype == torch.uint8 else s.detach().round().clamp(0, 255).to(torch.uint8) for s in srcs]
-        out = sweep.alloc_outputs()
+        # no merged maps: a soft run writes only their border
+        full = (ref_cam.height, ref_cam.width)
+        out = {k: torch.empty(full, dtype=torch.float32, device=sweep.device) for k in ("soft_invdepth", "soft_lse")}
         sweep.run([{"ref": ref, "srcs": u8, "camera_set": 0}], [out])
         ctx.sweep = sweep
         ctx.shapes = [tuple(s.shape) for s in srcs]
@@ -60,6 +64,7 @@ class SoftDepth(torch.autograd.Function):
         ctx.run_id = sweep.soft_run_id
         ctx.xi_dtype, ctx.xi_device = pose_xi.dtype, pose_xi.device
         ctx.mark_non_differentiable(out["soft_lse"])
+        ctx.set_materialize_grads(False)   # else every backward fills a zero gradient of lse
         # the backward also reads rho and lse of this run: saved, so that the
         # caller dropping them cannot free their memory
         ctx.save_for_backward(out["soft_invdepth"], out["soft_lse"])
@@ -67,14 +72,13 @@ class SoftDepth(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, grad_rho, grad_lse):
-        g = grad_rho if grad_rho is not None else None
-        if g is None:
-            return (None, None, None) + tuple(None for _ in ctx.shapes)
         # image gradients only for float sources that ask for them (inputs
         # 0..2 are the sweep, the reference and the pose)
         want = [f and ctx.needs_input_grad[3 + s] for s, f in enumerate(ctx.float_src)]
-        _ = ctx.saved_tensors   # rho and lse of this run, alive until the kernel has read them
-        gs, gp = ctx.sweep.soft_backward(g, ctx.shapes, image_grads=want, run_id=ctx.run_id)
+        rho, _ = ctx.saved_tensors   # rho and lse of this run, alive until the kernel has read them
+        if grad_rho is None:
+            grad_rho = torch.zeros_like(rho)
+        gs, gp = ctx.sweep.soft_backward(grad_rho, ctx.shapes, image_grads=want, run_id=ctx.run_id)
         g_src = tuple(gs)
         return (None, None, gp.to(device=ctx.xi_device, dtype=ctx.xi_dtype)) + g_src
 

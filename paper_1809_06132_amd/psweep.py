@@ -4,8 +4,10 @@ Argument marshalling only: every computation happens in libpsweep.so on the
 GPU.  Loading fails loudly when the library has not been built."""
 from __future__ import annotations
 
+import array
 import ctypes
 import functools
+import itertools
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -208,8 +210,11 @@ def psweep_set_chunks(ctx, level: int, n_chunks: int):
 
 def psweep_mask_boxes(ctx, camera_set: int, depth: int, code: int, pitch: int, boxes, stream: int = 0):
     """boxes: sequence of (x0, y0, x1, y1) half-open pixel rectangles."""
-    flat = [int(v) for b in boxes for v in b]
-    arr = (_i32 * max(1, len(flat)))(*flat)
+    flat = list(itertools.chain.from_iterable(boxes))
+    try:
+        arr = (_i32 * len(flat)).from_buffer(array.array("i", flat)) if flat else (_i32 * 1)()
+    except (TypeError, OverflowError):   # not all of them plain 32-bit integers
+        arr = (_i32 * len(flat))(*map(int, flat))
     _check(lib().psweep_mask_boxes(ctx, camera_set, depth, code, pitch, len(flat) // 4, arr, stream), ctx)
 
 
@@ -265,7 +270,7 @@ def psweep_plane_pixels_met(ctx, frames) -> int:
 
 def psweep_perturb_pose(R, t, xi):
     """(R', t') = (Exp(omega) R, Exp(omega) t + v) for xi = (v, omega), in FP64."""
-    Ra, ta, xa = (_d * 9)(*[float(v) for v in R]), (_d * 3)(*[float(v) for v in t]), (_d * 6)(*[float(v) for v in xi])
+    Ra, ta, xa = (_d * 9)(*map(float, R)), (_d * 3)(*map(float, t)), (_d * 6)(*map(float, xi))
     Ro, to = (_d * 9)(), (_d * 3)()
     _check(lib().psweep_perturb_pose(Ra, ta, xa, Ro, to))
     return list(Ro), list(to)
