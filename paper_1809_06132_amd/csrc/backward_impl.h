@@ -142,15 +142,31 @@ struct Backward {
     static constexpr size_t lds_bytes() {
         return lds_tile() + (size_t)(NCH * S + 1) * TYO * kWave * 4 + lds_patch();
     }
-    // Occupancy hint: the pose-only form of one or two sources leaves LDS for
-    // three workgroups per CU (6 waves per SIMD), which its registers reach
-    // when held to 80 (a few spills outside the hottest loops; C4's pose-only
-    // backward 0.40 -> 0.36 ms).  Elsewhere LDS holds the CU to two
-    // workgroups, and the hint would only add spills (1: no hint); so would it
-    // in the ground form, whose per-row values of both families need about
-    // 100 registers.
+    // Workgroups per CU: two by registers (128 a wave), or as many as LDS holds.
+    // The kernels are short of waves to hide their loads and LDS round trips
+    // behind, so registers are held to
+    // - 80 where LDS has room for three workgroups and the spills stay outside
+    //   the hottest loops: the fronto forms of one source and, pose only, of two
+    //   (640x480, 64 planes, 2 sources, pose only: 0.40 -> 0.36 ms; one source,
+    //   images too, 257 -> 252 us) and the pose-only ground form of one (411x307,
+    //   75 -> 70 us); not the ground form of two sources (131 -> 147) or with one
+    //   source's images (571 -> 620), whose values of both families need them;
+    // - 128 for the pose-only forms of four sources, which took up to 148 and so
+    //   ran one workgroup per CU (411x307, four sources, window 5 with ground
+    //   planes 368 -> 247 us, window 9 fronto 318 -> 202);
+    // - no more than the compiler's own number elsewhere (1: no hint).
+    static constexpr bool three() {
+        return ((!GND && (!GI || S == 1)) || (!GI && S == 1)) && 3 * (lds_bytes() + 1024) <= 160 * 1024;
+    }
+    // Whether a sample's warp (1 / den, |P|, the two slopes) is kept in registers
+    // from the forward recompute to the scatter, which the same lane does: where
+    // they cost no workgroup per CU (three or four sources, whose patches fill a
+    // CU by themselves, two fronto, one with ground planes).  It saves a square
+    // root, a reciprocal and the texel's second load a sample: 640x480, 64 planes,
+    // window 7: 474 -> 440 us with two sources, 1073 -> 1005 with three.
+    static constexpr bool KEEP = GI && (S >= 3 || (S == 2) == !GND);
     static constexpr int waves_per_eu() {
-        return !GI && !GND && 3 * (lds_bytes() + 1024) <= 160 * 1024 ? 6 : 1;
+        return three() ? 6 : !GI && S == 4 ? 4 : 1;
     }
 
     __device__ static void run(const JobDev *__restrict__ Jp, const float *__restrict__ gin,
@@ -395,6 +411,7 @@ struct Backward {
             // (fronto) or (n . (x, y, tau)) / (d - h) (ground): per-plane factor
             const float pf = fam ? 1.0f / (J.gd - theta) : theta;
             // ---- forward recompute: warped rows of every source into LDS ----
+            float k_inv[S][RS], k_m[S][RS], k_du[S][RS], k_dv[S][RS];   // KEEP: for the scatter
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 const PSW_CONST float *hm = cptr(J.htab) + (k * S + s) * 9;
@@ -422,7 +439,12 @@ struct Backward {
                                     (__float_as_uint(v) <= __float_as_uint(sd.hm1));
                     const uint32_t off = __umul24((uint32_t)(int)v, row_bytes) + (uint32_t)(int)u * Texel<IMG>::bytes;
                     const float al = __builtin_amdgcn_fractf(u), be = __builtin_amdgcn_fractf(v);
-                    const float b = Texel<IMG>::sample(rs, off, al, be);
+                    const typename Texel<IMG>::Raw q = Texel<IMG>::raw(rs, off);
+                    const float b = Texel<IMG>::blend(q, al, be);
+                    if (KEEP) {
+                        k_inv[s][i] = inv; k_m[s][i] = m;
+                        Texel<IMG>::slope(q, al, be, &k_du[s][i], &k_dv[s][i]);
+                    }
                     tile[((size_t)s * T + j) * kWave + lane] = ok ? b : -0.0f;
                 }
             }
@@ -567,20 +589,23 @@ struct Backward {
                     int a00 = -1, a10 = -1, a01 = -1, a11 = -1;
                     float c00 = 0.f, c10 = 0.f, c01 = 0.f, c11 = 0.f;
                     if ((gb != 0.0f) & !is_neg_zero(b)) {
-                        // recompute the warp of this sample with its derivatives
+                        // the warp of this sample again, with its derivatives
                         const float X = fmaf(h3x, tq[i], fmaf(h2x, yw[i], px));
                         const float Y = fmaf(h3y, tq[i], fmaf(h2y, yw[i], py));
                         const float Z = fmaf(h3z, tq[i], fmaf(h2z, yw[i], pz));
-                        const float m = __builtin_amdgcn_sqrtf(fmaf(X, X, fmaf(Y, Y, Z * Z)));
-                        const float den = fmaf(sd.xi, m, Z);
-                        const float inv = __builtin_amdgcn_rcpf(den);
+                        const float m = KEEP ? k_m[s][i] : __builtin_amdgcn_sqrtf(fmaf(X, X, fmaf(Y, Y, Z * Z)));
+                        const float inv = KEEP ? k_inv[s][i] : __builtin_amdgcn_rcpf(fmaf(sd.xi, m, Z));
                         const float u = fmaf(X * inv, sd.fx, sd.cx);
                         const float v = fmaf(Y * inv, sd.fy, sd.cy);
                         const int i0 = (int)u, v0 = (int)v;
                         const float al = __builtin_amdgcn_fractf(u), be = __builtin_amdgcn_fractf(v);
                         float dbu, dbv;
-                        Texel<IMG>::slope(rs, __umul24((uint32_t)v0, row_bytes) + (uint32_t)i0 * Texel<IMG>::bytes, al, be,
-                                          &dbu, &dbv);
+                        if (KEEP) {
+                            dbu = k_du[s][i]; dbv = k_dv[s][i];
+                        } else {
+                            Texel<IMG>::slope(rs, __umul24((uint32_t)v0, row_bytes) + (uint32_t)i0 * Texel<IMG>::bytes, al,
+                                              be, &dbu, &dbv);
+                        }
                         if (GI && gimg) {
                             const int pi = i0 - pox, pj = v0 - poy;
                             if ((uint32_t)pi < (uint32_t)(PW - 1) && (uint32_t)pj < (uint32_t)(PH - 1)) {

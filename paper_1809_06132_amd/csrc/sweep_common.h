@@ -260,7 +260,9 @@ struct Texel<0> {
         return blend(raw(rs, off), al, be);
     }
     __device__ static void slope(__amdgpu_buffer_rsrc_t rs, uint32_t off, float al, float be, float *du, float *dv) {
-        const auto q = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0);
+        slope(raw(rs, off), al, be, du, dv);
+    }
+    __device__ static void slope(Raw q, float al, float be, float *du, float *dv) {
         *du = fmaf(be, half_hi(q[1]), half_hi(q[0]));
         *dv = fmaf(al, half_hi(q[1]), half_lo(q[1]));
     }
@@ -292,7 +294,10 @@ struct Texel<1> {
         return blend(raw(rs, off), al, be);
     }
     __device__ static void slope(__amdgpu_buffer_rsrc_t rs, uint32_t off, float al, float be, float *du, float *dv) {
-        const Quad q = load(rs, off);
+        slope(raw(rs, off), al, be, du, dv);
+    }
+    __device__ static void slope(Raw r, float al, float be, float *du, float *dv) {
+        const Quad q = {__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[2]), __uint_as_float(r[3])};
         *du = fmaf(be, q.p11 - q.p01, (1.0f - be) * (q.p10 - q.p00));
         *dv = fmaf(al, q.p11 - q.p10, (1.0f - al) * (q.p01 - q.p00));
     }
