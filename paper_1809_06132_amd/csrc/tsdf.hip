@@ -267,7 +267,10 @@ __global__ __launch_bounds__(256) void tsdf_extract_kernel(TsdfDev T, float *out
 }
 
 // allocated blocks (counted now: the integrations keep no count of them) and
-// the blocks listed by the last integration
+// the blocks listed by the last integration.  Counting them during the
+// integrations would cost each of those 4.5 us of atomics; this costs a call of
+// stats 6 us more (7.4 us of 22,500 blocks; the same with 16 loads in flight a
+// thread).
 __global__ __launch_bounds__(1024) void tsdf_stats_kernel(TsdfDev T, int32_t *out) {
     __shared__ int total;
     if (threadIdx.x == 0) total = 0;

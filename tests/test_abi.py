@@ -3,6 +3,7 @@ declares, and rejects bad configurations on the host before touching a GPU."""
 import os
 import re
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -142,3 +143,23 @@ def test_tsdf_rejects_bad_config():
     assert L.psweep_tsdf_integrate(ts, cam, pose, far, 1, 0, None) == psweep.EINVAL
     assert psweep.psweep_tsdf_last_error(ts)
     psweep.psweep_tsdf_destroy(ts)
+
+
+@pytest.mark.parametrize("boxes,flat", [
+    ([], []), ([(1, 2, 3, 4), (-5, 6, 7, 8)], [1, 2, 3, 4, -5, 6, 7, 8]), ([(1.7, -2.7, 3, 4)], [1, -2, 3, 4]),
+    (np.array([[1, 2, 3, 4]]), [1, 2, 3, 4]), (((i, i, 9, 9) for i in range(2)), [0, 0, 9, 9, 1, 1, 9, 9]),
+    ([(2 ** 40 + 5, 2, 3, 4)], [5, 2, 3, 4]),
+])
+def test_boxes_of_any_number_type_go_over_as_int32(monkeypatch, boxes, flat):
+    from paper_1809_06132_amd import psweep as P
+    seen = {}
+
+    class Fake:
+        @staticmethod
+        def psweep_mask_boxes(ctx, cs, depth, code, pitch, n, arr, stream):
+            seen["boxes"] = list(arr)[:4 * n]
+            return P.OK
+
+    monkeypatch.setattr(P, "lib", lambda: Fake)
+    P.psweep_mask_boxes(None, 0, 1, 0, 0, boxes)
+    assert seen["boxes"] == flat
