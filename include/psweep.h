@@ -221,8 +221,11 @@ psweep_status psweep_run(psweep_ctx *ctx, const psweep_frame *frames, int32_t n_
  * sources needs about 31 MiB; EUNSUPPORTED in soft mode.  Every call on one
  * GPU shares that GPU's array, which keeps the last call's contents: calls
  * (from any context) that overlap on one GPU race, so order them on one
- * stream; a call after psweep_run on the same context sets its tables up
- * again.  Calls no hipMalloc or hipFree. */
+ * stream; a call after psweep_run on the same context, or after another
+ * context's call, sets its tables up again.  A capture of the caller's own
+ * records what the call enqueues: make the same call once before it, so that no
+ * table upload is recorded, and replay only while no other call has used the
+ * array since.  Calls no hipMalloc or hipFree. */
 psweep_status psweep_run_noalloc(psweep_ctx *ctx, const psweep_frame *frames, int32_t n_frames,
                                  const psweep_output *out, void *hip_stream);
 

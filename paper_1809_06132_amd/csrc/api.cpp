@@ -7,9 +7,11 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <numeric>
 #include <new>
 #include <string>
@@ -39,6 +41,16 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 thread_local std::string g_create_error;
+std::atomic<uint64_t> g_contexts{0};
+
+// The context (its id) whose tables and plane setup a GPU's static scratch
+// holds: every context's psweep_run_noalloc writes its own there.  Held while a
+// run is enqueued, so that the runs of several threads follow one another whole.
+struct ScratchOwner {
+    std::mutex mu;
+    uint64_t id = 0;
+};
+ScratchOwner g_scratch_owner[kMaxDevices];
 
 struct CamSet {
     bool defined = false;
@@ -115,6 +127,7 @@ struct Layout {
 }  // namespace
 
 struct psweep_ctx {
+    uint64_t id = 0;   // of this process, never used again
     psweep_config cfg{};
     std::vector<CamSet> sets;
     int P[PSWEEP_MAX_LEVELS] = {0, 0};
@@ -346,6 +359,7 @@ psweep_status psweep_create(const psweep_config *cfg, psweep_ctx **out) {
     if (st != PSWEEP_OK) return st;
     psweep_ctx *ctx = new (std::nothrow) psweep_ctx();
     if (!ctx) return fail(nullptr, PSWEEP_ENOMEM, "host allocation failed");
+    ctx->id = ++g_contexts;
     ctx->cfg = *cfg;
     ctx->sets.resize(cfg->max_camera_sets);
     const int W = cfg->max_width, H = cfg->max_height;
@@ -1178,8 +1192,8 @@ psweep_status run_on(psweep_ctx *ctx, const psweep_frame *frames, int32_t n_fram
     if (st != PSWEEP_OK) return st;
     std::vector<JobDev> hj(blob.nj);
     std::memcpy(hj.data(), blob.bytes.data() + blob.jobs, sizeof(JobDev) * blob.nj);
-    // upload the tables when they changed (the device copy stays valid: only
-    // runs on this memory write this region)
+    // upload the tables when they changed (the device copy stays valid: the
+    // workspace is this context's own, and the static scratch has its owner)
     const bool changed = blob.bytes != ctx->last_table;
     if (changed) {
         const int b = ctx->staging_idx;
@@ -1239,6 +1253,14 @@ psweep_status psweep_run_noalloc(psweep_ctx *ctx, const psweep_frame *frames, in
                     "psweep_run_noalloc: this context needs " + std::to_string(ctx->lean.need) +
                         " bytes of scratch, more than the library's static " + std::to_string(bytes) +
                         " (smaller max_width / max_height / max_sources / max_frames)");
+    int dev = 0;   // psw_static_scratch knows it: below kMaxDevices
+    PSW_HIP(hipGetDevice(&dev), "current device");
+    ScratchOwner &owner = g_scratch_owner[dev];
+    std::lock_guard<std::mutex> lock(owner.mu);
+    if (owner.id != ctx->id) {
+        ctx->last_base = nullptr;   // whatever this context had there is overwritten
+        owner.id = ctx->id;
+    }
     return run_on(ctx, frames, n_frames, out, hip_stream, (char *)scratch, &ctx->lean);
 }
 

@@ -415,20 +415,20 @@ __global__ void mask_kernel(MaskDev M) {
 }  // namespace psw
 
 // Scratch of psweep_run_noalloc: job tables, counters, level images,
-// textures, level maps and, as far as they fit, partial states of one run, for callers that cannot allocate.
+// textures, level maps and, as far as they fit, partial states of one run, for
+// callers that cannot allocate.
 // Every GPU the library runs on holds one copy until the process ends; host
 // code uses its device address (from hipGetSymbolAddress, taken once per
 // device with that device current), never the array's name.
 static __device__ __align__(256) unsigned char scratch[psw::kStaticScratchBytes];
 
 extern "C" hipError_t psw_static_scratch(void **ptr, size_t *bytes) {
-    constexpr int kMaxDevices = 64;
     static std::mutex mu;
-    static void *addr[kMaxDevices] = {};
+    static void *addr[psw::kMaxDevices] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    if (dev < 0 || dev >= psw::kMaxDevices) return hipErrorInvalidDevice;
     std::lock_guard<std::mutex> lock(mu);
     if (!addr[dev]) {
         void *p = nullptr;

@@ -75,6 +75,7 @@ constexpr int kCounterStride = 32;
 constexpr int kPartWords = 7;   // c1, kb, c2, cm, cp, first, last (soft: max, sum, sum*theta)
 constexpr int kMaxChunks = 8;
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;   // of psweep_run_noalloc, per GPU
+constexpr int kMaxDevices = 64;                            // GPUs that may hold one
 
 // plane range [kb, ke) of chunk c of a job (chunks never straddle families)
 __host__ __device__ inline void chunk_range(int n_fronto, int n_ground, int nch_f, int nch_g, int c, int *kb,
