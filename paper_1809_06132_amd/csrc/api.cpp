@@ -707,8 +707,9 @@ int resident_blocks(psweep_ctx *ctx, const KernelEntry *e) {
 // kernel), and with which kernel; *tiles: the run's tiles.  A persistent config
 // always does (or the run fails at its launch).  A grid config does where that
 // kernel is built for the run: winner-take-all on 8-bit images, windows 7 and
-// 9, one source count, one tile shape, and neither cost volumes nor per-launch
-// timing asked for, which belong to a launch per job.  The maps are the same,
+// 9, one source count, one tile shape (one that the grid kernels have too: the
+// others stay refused), and neither cost volumes nor per-launch timing asked
+// for, which belong to a launch per job.  The maps are the same,
 // bit for bit, and the levels of a run, or its plane chunks, then fill the chip
 // together (per pass, grids then queues: two levels of 1024x768, 3 sources, 323
 // and 286 us; of 1024x544, 4 sources, 356 and 297 us; one of 1024x768, 762 and
@@ -734,7 +735,8 @@ bool one_launch(psweep_ctx *ctx, const psweep_frame *frames, int nf, const pswee
             const int hw = L.window / 2, txo = kWave - 2 * hw, tyo = ctx->tile_rows[l] * ctx->tile_waves[l];
             *tiles += (int64_t)(std::max(0, rc.w - 2 * hw + txo - 1) / txo) * (std::max(0, rc.h - 2 * hw + tyo - 1) / tyo);
             fits = fits && (L.window == 7 || L.window == 9) && !out[f].cost_volume[l] &&
-                   ctx->tile_rows[l] == ctx->tile_rows[0] && ctx->tile_waves[l] == ctx->tile_waves[0];
+                   ctx->tile_rows[l] == ctx->tile_rows[0] && ctx->tile_waves[l] == ctx->tile_waves[0] &&
+                   find_kernel(L.window, ctx->tile_rows[l], ctx->tile_waves[l], C.n_src, cfg.storage, 0, 0, 0);
         }
     }
     *kernel = find_kernel(0, ctx->tile_rows[0], ctx->tile_waves[0], n_src, cfg.storage, 0, 1, 0);

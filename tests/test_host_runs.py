@@ -29,3 +29,39 @@ def test_noalloc_contexts_taking_turns(tmp_path):
         print("ok")
     """)
     assert "ok" in out
+
+
+def test_tiles_without_a_grid_kernel_stay_refused(tmp_path):
+    """A grid config with a tile shape that no grid kernel has is refused,
+    whatever the persistent kernels are built for and however the run would be
+    launched; a persistent config still takes the shapes it has."""
+    out = host_run(tmp_path, """
+        two = [(24, 0.5, 10, 7, 2, (0, 0, 0, 0)), (24, 0.5, 10, 9, 1, (128, 96, 256, 192))]
+        one = [(60, 0.5, 20, 9, 1, (0, 0, 0, 0))]
+        refused = 0
+        for levels in (two, one):
+            for store in (0, 1, 2):
+                for S in (1, 2, 3, 4):
+                    for tile in ((4, 4), (8, 4), (4, 8), (2, 8), (16, 4), (8, 2)):
+                        got = {}
+                        for launch, timed in ((0, True), (0, False), (1, False)):
+                            r = Run(config(512, 384, S, levels, storage=store, launch=launch), 1 << 32)
+                            for l in range(len(levels)):
+                                P.psweep_set_tile(r.ctx, l, *tile)
+                            P.psweep_set_timing(r.ctx, timed)
+                            try:
+                                r()
+                                got[launch, timed] = 0
+                            except P.PsweepError as e:
+                                got[launch, timed] = e.status
+                            P.psweep_destroy(r.ctx)
+                        # a timed run is a launch per job: the grid kernels decide
+                        assert got[0, False] == got[0, True], (len(levels), store, S, tile, got)
+                        assert set(got.values()) <= {0, P.EUNSUPPORTED}
+                        refused += got[0, False] != 0
+                        if tile == (4, 8) and store == 2 and S >= 3:
+                            assert got[0, False] == P.EUNSUPPORTED and got[1, False] == 0
+        assert refused
+        print("ok")
+    """)
+    assert "ok" in out
