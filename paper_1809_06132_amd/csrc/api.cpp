@@ -703,50 +703,6 @@ int resident_blocks(psweep_ctx *ctx, const KernelEntry *e) {
     return n;
 }
 
-// Whether a run's sweeps go into one launch over item queues (the persistent
-// kernel), and with which kernel; *tiles: the run's tiles.  A persistent config
-// always does (or the run fails at its launch).  A grid config does where that
-// kernel is built for the run: winner-take-all on 8-bit images, windows 7 and
-// 9, one source count, one tile shape (one that the grid kernels have too: the
-// others stay refused), and neither cost volumes nor per-launch timing asked
-// for, which belong to a launch per job.  The maps are the same,
-// bit for bit, and the levels of a run, or its plane chunks, then fill the chip
-// together (per pass, grids then queues: two levels of 1024x768, 3 sources, 323
-// and 286 us; of 1024x544, 4 sources, 356 and 297 us; one of 1024x768, 762 and
-// 711 us).  One job whose items are all resident at once stays a grid, with no
-// counters at all (320x256, one source: 29.3 against 31.0 us).
-bool one_launch(psweep_ctx *ctx, const psweep_frame *frames, int nf, const psweep_output *out,
-                const KernelEntry **kernel, int64_t *tiles) {
-    const psweep_config &cfg = ctx->cfg;
-    bool fits = cfg.mode == PSWEEP_MODE_WTA && cfg.image_format == PSWEEP_IMAGE_U8 && !ctx->timing;
-    int n_src = 0;
-    *tiles = 0;
-    for (int f = 0; f < nf; ++f) {
-        const int cs = frames[f].camera_set;
-        if (cs < 0 || cs >= (int)ctx->sets.size()) continue;   // refused when the tables are built
-        const CamSet &C = ctx->sets[cs];
-        if (f == 0) n_src = C.n_src;
-        fits = fits && C.n_src == n_src;
-        for (int l = 0; l < cfg.n_levels; ++l) {
-            const psweep_level &L = cfg.level[l];
-            int cw = L.crop_w, ch = L.crop_h;
-            if (l == 1 && C.crop_set) { cw = C.crop[2]; ch = C.crop[3]; }
-            const LevelCam rc = level_cam(C.ref, L.downsample, 0, 0, cw, ch);
-            const int hw = L.window / 2, txo = kWave - 2 * hw, tyo = ctx->tile_rows[l] * ctx->tile_waves[l];
-            *tiles += (int64_t)(std::max(0, rc.w - 2 * hw + txo - 1) / txo) * (std::max(0, rc.h - 2 * hw + tyo - 1) / tyo);
-            fits = fits && (L.window == 7 || L.window == 9) && !out[f].cost_volume[l] &&
-                   ctx->tile_rows[l] == ctx->tile_rows[0] && ctx->tile_waves[l] == ctx->tile_waves[0] &&
-                   find_kernel(L.window, ctx->tile_rows[l], ctx->tile_waves[l], C.n_src, cfg.storage, 0, 0, 0);
-        }
-    }
-    *kernel = find_kernel(0, ctx->tile_rows[0], ctx->tile_waves[0], n_src, cfg.storage, 0, 1, 0);
-    if (cfg.launch == PSWEEP_LAUNCH_PERSISTENT) return true;
-    if (!fits || !*kernel) return false;
-    const bool one_job = nf * cfg.n_levels == 1;
-    return !one_job || *tiles * std::min(kMaxChunks, std::max(1, ctx->P[0] / 4)) >
-                           (int64_t)ctx->n_cu * resident_blocks(ctx, *kernel);
-}
-
 // How many chunks the planes of a level are cut into (automatic count): of at
 // least 4 planes each.  An item costs about three of its (plane, source) steps
 // beside its own work (set-up, first warp, partial state), so that few long
@@ -775,6 +731,87 @@ int plane_chunks(const psweep_ctx *ctx, int64_t tiles, int P, int S, bool queues
         nch = std::max<int64_t>(4, std::min<int64_t>(most, (int64_t)std::ceil(std::sqrt(work / 2.0))));
     }
     return (int)std::max<int64_t>(1, std::min<int64_t>(nch, most));
+}
+
+// The plane chunks of level l in a run of `tiles` tiles (of the level, or of the
+// whole run where its items go into queues): as many as the context sets, else
+// plane_chunks, as far as partial states have room, dealt to the two families.
+// One chunk: both 0.  Soft mode's automatic count: enough workgroups for about
+// 28 waves per SIMD (its outputs depend on the number, since the chunks' merge
+// rounds).
+void split_planes(const psweep_ctx *ctx, int l, int64_t tiles, int n_src, bool queues, int *nch_f, int *nch_g) {
+    const psweep_level &L = ctx->cfg.level[l];
+    const bool soft = ctx->cfg.mode == PSWEEP_MODE_SOFT;
+    const int P = L.n_fronto + L.n_ground;
+    const int most = ctx->lay->part_chunks;   // under 2: one pass
+    int nch = most < 2 ? 1 : ctx->chunks[l];
+    if (nch == 0 && !soft) {
+        nch = plane_chunks(ctx, tiles, P, n_src, queues);
+    } else if (nch == 0) {
+        const long long target = 28LL * ctx->n_cu * 4;
+        const long long have = (long long)tiles * ctx->tile_waves[l];
+        nch = have > 0 ? (int)((target + have - 1) / have) : 1;
+        nch = std::max(1, std::min(nch, kMaxChunks));
+    }
+    if (soft && nch > 1) nch = std::min(nch, std::max(1, L.n_fronto / 2));
+    nch = std::min(nch, std::max(most, 1));
+    *nch_f = *nch_g = 0;
+    if (nch <= 1) return;
+    const int cs = (P + nch - 1) / nch;
+    int f = L.n_fronto > 0 ? (L.n_fronto + cs - 1) / cs : 0;
+    int g = L.n_ground > 0 ? (L.n_ground + cs - 1) / cs : 0;
+    while (f + g > most) { if (f >= g) --f; else --g; }
+    if (f + g <= 1) return;
+    *nch_f = f;
+    *nch_g = g;
+}
+
+// Whether a run's sweeps go into one launch over item queues (the persistent
+// kernel), and with which kernel; *tiles: the run's tiles.  A persistent config
+// always does (or the run fails at its launch).  A grid config does where that
+// kernel is built for the run: winner-take-all on 8-bit images, windows 7 and
+// 9, one source count, one tile shape (one that the grid kernels have too: the
+// others stay refused), and neither cost volumes nor per-launch timing asked
+// for, which belong to a launch per job.  The maps are the same,
+// bit for bit, and the levels of a run, or its plane chunks, then fill the chip
+// together (per pass, grids then queues: two levels of 1024x768, 3 sources, 323
+// and 286 us; of 1024x544, 4 sources, 356 and 297 us; one of 1024x768, 762 and
+// 711 us).  One job whose items, in the chunks that its grid would have, are all
+// resident at once stays a grid, with no counters at all (grid against queues,
+// per pass: 320x256, one source, 29.3 and 31.0 us; 586x326, 32 planes, 39 and
+// 44; in one chunk set by the caller, 1024x768, one source, 64 planes, 152 and
+// 179; 640x480, three sources, 94 planes, 448 and 446).
+bool one_launch(psweep_ctx *ctx, const psweep_frame *frames, int nf, const psweep_output *out,
+                const KernelEntry **kernel, int64_t *tiles) {
+    const psweep_config &cfg = ctx->cfg;
+    bool fits = cfg.mode == PSWEEP_MODE_WTA && cfg.image_format == PSWEEP_IMAGE_U8 && !ctx->timing;
+    int n_src = 0;
+    *tiles = 0;
+    for (int f = 0; f < nf; ++f) {
+        const int cs = frames[f].camera_set;
+        if (cs < 0 || cs >= (int)ctx->sets.size()) continue;   // refused when the tables are built
+        const CamSet &C = ctx->sets[cs];
+        if (f == 0) n_src = C.n_src;
+        fits = fits && C.n_src == n_src;
+        for (int l = 0; l < cfg.n_levels; ++l) {
+            const psweep_level &L = cfg.level[l];
+            int cw = L.crop_w, ch = L.crop_h;
+            if (l == 1 && C.crop_set) { cw = C.crop[2]; ch = C.crop[3]; }
+            const LevelCam rc = level_cam(C.ref, L.downsample, 0, 0, cw, ch);
+            const int hw = L.window / 2, txo = kWave - 2 * hw, tyo = ctx->tile_rows[l] * ctx->tile_waves[l];
+            *tiles += (int64_t)(std::max(0, rc.w - 2 * hw + txo - 1) / txo) * (std::max(0, rc.h - 2 * hw + tyo - 1) / tyo);
+            fits = fits && (L.window == 7 || L.window == 9) && !out[f].cost_volume[l] &&
+                   ctx->tile_rows[l] == ctx->tile_rows[0] && ctx->tile_waves[l] == ctx->tile_waves[0] &&
+                   find_kernel(L.window, ctx->tile_rows[l], ctx->tile_waves[l], C.n_src, cfg.storage, 0, 0, 0);
+        }
+    }
+    *kernel = find_kernel(0, ctx->tile_rows[0], ctx->tile_waves[0], n_src, cfg.storage, 0, 1, 0);
+    if (cfg.launch == PSWEEP_LAUNCH_PERSISTENT) return true;
+    if (!fits || !*kernel) return false;
+    if (nf * cfg.n_levels > 1) return true;
+    int f, g;
+    split_planes(ctx, 0, *tiles, n_src, false, &f, &g);
+    return *tiles * std::max(1, f + g) > (int64_t)ctx->n_cu * resident_blocks(ctx, *kernel);
 }
 
 // Build the per-run tables (host side) for `frames`: job, setup, prep,
@@ -895,34 +932,10 @@ psweep_status build_tables(psweep_ctx *ctx, const psweep_frame *frames, int nf, 
             J.tiles_x = rc.w > 2 * hw ? (rc.w - 2 * hw + TXO - 1) / TXO : 0;
             J.tiles_y = rc.h > 2 * hw ? (rc.h - 2 * hw + TYO - 1) / TYO : 0;
             J.rows = rows; J.waves = waves;
-            // plane chunks, where the context sets none (see plane_chunks).  Soft
-            // mode: enough workgroups for about 28 waves per SIMD (its outputs
-            // depend on the number, since the chunks' merge rounds).
-            {
-                const int ntile = J.tiles_x * J.tiles_y;
-                const int most = ctx->lay->part_chunks;   // under 2: one pass
-                int nch = most < 2 ? 1 : ctx->chunks[l];
-                if (nch == 0 && cfg.mode != PSWEEP_MODE_SOFT) {
-                    nch = plane_chunks(ctx, blob.queues ? run_tiles : ntile, P, C.n_src, blob.queues);
-                } else if (nch == 0) {
-                    const long long target = 28LL * ctx->n_cu * 4;
-                    const long long have = (long long)ntile * waves;
-                    nch = have > 0 ? (int)((target + have - 1) / have) : 1;
-                    nch = std::max(1, std::min(nch, kMaxChunks));
-                }
-                if (cfg.mode == PSWEEP_MODE_SOFT && nch > 1) nch = std::min(nch, std::max(1, L.n_fronto / 2));
-                J.nch_f = 0; J.nch_g = 0;
-                nch = std::min(nch, std::max(most, 1));
-                if (nch > 1) {
-                    const int cs = (P + nch - 1) / nch;
-                    J.nch_f = L.n_fronto > 0 ? (L.n_fronto + cs - 1) / cs : 0;
-                    J.nch_g = L.n_ground > 0 ? (L.n_ground + cs - 1) / cs : 0;
-                    while (J.nch_f + J.nch_g > most) { if (J.nch_f >= J.nch_g) --J.nch_f; else --J.nch_g; }
-                    if (J.nch_f + J.nch_g <= 1) { J.nch_f = 0; J.nch_g = 0; }
-                }
-                J.part = (float *)(slot + Y.s_part[l]);
-                orders.push_back(&item_order(ctx, rc, L, J, blob.queues));
-            }
+            split_planes(ctx, l, blob.queues ? run_tiles : (int64_t)J.tiles_x * J.tiles_y, C.n_src, blob.queues,
+                         &J.nch_f, &J.nch_g);
+            J.part = (float *)(slot + Y.s_part[l]);
+            orders.push_back(&item_order(ctx, rc, L, J, blob.queues));
             for (int s = 0; s < C.n_src; ++s) {
                 const LevelCam sc = level_cam(C.src[s], ds, 0, 0, 0, 0);
                 SrcDev &D = J.src[s];

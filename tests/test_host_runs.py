@@ -65,3 +65,60 @@ def test_tiles_without_a_grid_kernel_stay_refused(tmp_path):
         print("ok")
     """)
     assert "ok" in out
+
+
+def test_one_job_that_fits_the_chip_is_a_grid(tmp_path):
+    """A grid config's single job goes into the item queues only where the items
+    of the grid that it would be, in the chunks that it would have, are more
+    than the chip holds (here 256 CUs of four workgroups); several jobs always
+    do.  The chunks a caller sets, and those the static scratch has room for,
+    count as they are."""
+    out = host_run(tmp_path, """
+        def form(w, h, S, planes, win=7, chunks=0, call=P.psweep_run, frames=1, **kw):
+            r = Run(config(w, h, S, [(planes, 0.5, 0, win, 1, (0, 0, 0, 0))], frames=frames, **kw), 1 << 32,
+                    workspace=call is P.psweep_run)
+            P.psweep_set_chunks(r.ctx, 0, chunks)
+            got = sweeps(r(call))
+            assert all(g["inside"] == 1 for g in got), got
+            P.psweep_destroy(r.ctx)
+            return got[0]["form"], got[0]["chunks"], got[0]["items"]
+
+        # 320x256, window 7: 6 x 16 tiles
+        assert form(320, 256, 1, 32) == ("grid", 7, 672)
+        # 10 x 20 tiles: five chunks, not the eight that 32 planes allow
+        assert form(586, 326, 1, 32) == ("grid", 5, 1000)
+        assert form(586, 326, 1, 32, chunks=5) == ("grid", 5, 1000)
+        assert form(586, 326, 1, 32, chunks=6)[0] == "queues"
+        assert form(640, 480, 3, 96, chunks=1)[:2] == ("grid", 1)
+        assert form(640, 480, 3, 96)[0] == "queues"
+        assert form(640, 480, 3, 96, frames=2, chunks=1)[0] == "queues"
+        # the static scratch with no room for chunks
+        assert form(1024, 896, 4, 200, call=P.psweep_run_noalloc) == ("grid", 1, 1008)
+        assert form(1152, 896, 3, 200, call=P.psweep_run_noalloc) == ("queues", 1, 1120)
+        print("ok")
+    """)
+    assert "ok" in out
+
+
+def test_queues_hold_every_item_once(tmp_path):
+    """Runs in the item queues: one row of tiles, fewer items than queues, a
+    level too small for a tile, many frames; every job's items are all there."""
+    out = host_run(tmp_path, """
+        small = (16, 0.5, 0, 7, 1, (0, 0, 0, 0))
+        for w, h, S, levels, frames, kw in (
+                (640, 22, 2, [(64, 0.5, 0, 9, 1, (0, 0, 0, 0))], 1, dict(launch=1)),        # 12 x 1 tiles
+                (60, 22, 1, [(8, 0.5, 0, 7, 1, (0, 0, 0, 0))], 1, dict(launch=1)),          # one tile, two chunks
+                (60, 22, 1, [(3, 0.5, 0, 7, 1, (0, 0, 0, 0))], 1, dict(launch=1)),          # one item
+                (40, 12, 2, [(8, 0.5, 0, 7, 2, (0, 0, 0, 0)), (8, 0.5, 0, 7, 1, (4, 0, 16, 12))], 1, {}),
+                (320, 200, 2, [small], 16, {}), (1024, 544, 4, [(64, 0.5, 30, 7, 2, (0, 0, 0, 0)),
+                                                               (64, 0.5, 30, 9, 1, (256, 128, 512, 272))], 1, {})):
+            r = Run(config(w, h, S, levels, frames=frames, **kw), 1 << 32)
+            got = sweeps(r())
+            assert len(got) == frames * len(levels) and all(g["form"] == "queues" for g in got), got
+            for g, lv in zip(got, levels * frames):
+                hw = lv[3] // 2
+                tiles = max(0, -(-(int(g["w"]) - 2 * hw) // (64 - 2 * hw))) * max(0, -(-(int(g["h"]) - 2 * hw) // 16))
+                assert g["inside"] == 1 and g["items"] == tiles * g["chunks"], (g, tiles)
+        print("ok")
+    """)
+    assert "ok" in out
