@@ -43,7 +43,10 @@
 // neighbouring samples share in registers first leaves one atomic in four, but
 // the kernel is bound by its vector instructions, and the folding took more of
 // them than it saved (640x480, two sources, 64 planes, window 7: 571 us with it,
-// 492 us without).  On a level with ground planes the taps are folded (a lane's
+// 492 us without).  These taps are rounded to nearest, since four truncations a
+// sample would add up to a bias (64 x 20 pixels, 16 planes, one pixel's gradient
+// far above the others': 4,329 units in all, 155 rounded; the same time).  On a
+// level with ground planes the taps are folded (a lane's
 // bottom taps with its top taps of the next sample row, its right taps with the
 // left taps of the lane to its right): theta has no bound near the horizon, the
 // scale is coarse for it (a conversion's error reaches 1e-5 of a gradient image,
@@ -617,11 +620,15 @@ struct Backward {
                                     c00 = g0 * (1.0f - be); c10 = g1 * (1.0f - be);
                                     c01 = g0 * be; c11 = g1 * be;
                                 } else {
+                                    // four conversions a sample: rounded to
+                                    // nearest, half a unit of the taps' sign (gs's,
+                                    // the weights have none) in the FMA
+                                    const float half = __builtin_copysignf(0.5f, gs);
                                     unsigned long long *const q = pat + pj * PW + pi;
-                                    ladd(q, g0 * (1.0f - be));
-                                    ladd(q + 1, g1 * (1.0f - be));
-                                    ladd(q + PW, g0 * be);
-                                    ladd(q + PW + 1, g1 * be);
+                                    ladd(q, fmaf(g0, 1.0f - be, half));
+                                    ladd(q + 1, fmaf(g1, 1.0f - be, half));
+                                    ladd(q + PW, fmaf(g0, be, half));
+                                    ladd(q + PW + 1, fmaf(g1, be, half));
                                 }
                             } else {
                                 const int i1 = i0 + 1 < sd.w ? i0 + 1 : sd.w - 1;
