@@ -67,13 +67,23 @@ __global__ void tsdf_reset_kernel(TsdfDev T) {
     if (blockIdx.x == 0 && threadIdx.x == 0) T.counters[0] = 0;
 }
 
+// a word that threads of other waves read and write in the same launch, in no
+// order that matters: relaxed, and served by the caches like any other (the
+// same instructions)
+template <typename V> __device__ __forceinline__ V load_shared(const V *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+template <typename V> __device__ __forceinline__ void store_shared(V *p, V v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
 // One thread per depth pixel: walk the blocks its truncation segment crosses
 // (a 3-D digital differential analyser in block units), mark them seen and
 // allocate those that are not.  Bound by the latency of its reads of the slots'
 // keys and marks.  Every thread that meets a block writes the same words, none
-// of which depends on what the others wrote, so the reads are plain cached
-// loads (a thread that misses another's stores only repeats them) and there is
-// no compare-and-swap.  The rest is arithmetic: 15 divisions a pixel.  1024x768:
+// of which depends on what the others wrote, so the reads are cached loads (a
+// thread that misses another's stores only repeats them) and there is no
+// compare-and-swap.  The rest is arithmetic: 15 divisions a pixel.  1024x768:
 // 18.3 (11 in the best launches) -> 11 us.  Also clears the next kernel's counter.
 __global__ __launch_bounds__(256) void tsdf_alloc_kernel(TsdfDev T) {
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.y == 0 && threadIdx.x == 0) T.counters[0] = 0;
@@ -115,14 +125,14 @@ __global__ __launch_bounds__(256) void tsdf_alloc_kernel(TsdfDev T) {
         if (cur[0] >= 0 && cur[0] < T.nb[0] && cur[1] >= 0 && cur[1] < T.nb[1] && cur[2] >= 0 && cur[2] < T.nb[2]) {
             const int s = (place(T, 2, cur[2]) * T.nb[1] + place(T, 1, cur[1])) * T.nb[0] + place(T, 0, cur[0]);
             const unsigned long long key = pack_block(T.b0[0] + cur[0], T.b0[1] + cur[1], T.b0[2] + cur[2]);
-            const unsigned long long had = T.keys[s];
-            const int marked = T.seen[s];
+            const unsigned long long had = load_shared(T.keys + s);
+            const int marked = load_shared(T.seen + s);
             if (had != key) {
-                T.count[s] = 0;
-                T.fresh[s] = 1;
-                T.keys[s] = key;
+                store_shared(T.count + s, 0);
+                store_shared(T.fresh + s, 1);
+                store_shared(T.keys + s, key);
             }
-            if (!marked) T.seen[s] = 1;
+            if (!marked) store_shared(T.seen + s, 1);
         }
         const int ax = tmax[0] <= tmax[1] ? (tmax[0] <= tmax[2] ? 0 : 2) : (tmax[1] <= tmax[2] ? 1 : 2);
         if (tmax[ax] > 1.0f) break;
