@@ -276,22 +276,33 @@ __global__ __launch_bounds__(256) void tsdf_extract_kernel(TsdfDev T, float *out
     }
 }
 
-// allocated blocks (counted now: the integrations keep no count of them) and
-// the blocks listed by the last integration.  Counting them during the
-// integrations would cost each of those 4.5 us of atomics; this costs a call of
-// stats 6 us more (7.4 us of 22,500 blocks; the same with 16 loads in flight a
-// thread).
+// Allocated blocks (counted now: the integrations keep no count of them, which
+// would cost each of those 4.5 us of atomics) and the blocks listed by the last
+// integration.  The workgroups' counts are added to a cleared word; one
+// workgroup, for maps whose keys it reads in less than that launch takes, writes
+// it itself (a call: 22,500 slots 7.4 us, 32,768 8.6; one workgroup and then
+// several: 65,536 slots 12.0 and 8.8, 262,144 34.6 and 8.7, 2^22 1,127 and 11.8).
+__global__ void tsdf_stats_clear_kernel(TsdfDev T, int32_t *out) {
+    if (threadIdx.x == 0) {
+        out[0] = 0;
+        out[1] = T.counters[0];
+    }
+}
 __global__ __launch_bounds__(1024) void tsdf_stats_kernel(TsdfDev T, int32_t *out) {
     __shared__ int total;
     if (threadIdx.x == 0) total = 0;
     __syncthreads();
     int n = 0;
-    for (int s = threadIdx.x; s < T.nslots; s += 1024) n += T.keys[s] != 0ull;
+    for (int s = blockIdx.x * 1024 + threadIdx.x; s < T.nslots; s += gridDim.x * 1024) n += T.keys[s] != 0ull;
     atomicAdd(&total, n);
     __syncthreads();
     if (threadIdx.x == 0) {
-        out[0] = total;
-        out[1] = T.counters[0];
+        if (gridDim.x > 1) {
+            atomicAdd(out, total);
+        } else {
+            out[0] = total;
+            out[1] = T.counters[0];
+        }
     }
 }
 
@@ -306,6 +317,7 @@ const void *psw_tsdf_kernel(int which) {
     case 3: return (const void *)&psw::tsdf_integrate_kernel;
     case 4: return (const void *)&psw::tsdf_extract_kernel;
     case 5: return (const void *)&psw::tsdf_stats_kernel;
+    case 6: return (const void *)&psw::tsdf_stats_clear_kernel;
     }
     return nullptr;
 }

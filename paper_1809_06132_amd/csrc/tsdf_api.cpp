@@ -3,6 +3,7 @@
 // list visible blocks -> integrate).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -20,6 +21,7 @@ namespace {
 thread_local std::string g_tsdf_create_error;
 constexpr size_t kAlign = 256;
 size_t align_up(size_t n) { return (n + kAlign - 1) / kAlign * kAlign; }
+constexpr int kStatsOne = 32768, kStatsSlots = 4096;   // see psweep_tsdf_stats
 
 }  // namespace
 
@@ -232,7 +234,15 @@ psweep_status psweep_tsdf_stats(psweep_tsdf *ts, int32_t *d_stats, void *hip_str
     if (!ts->integrated) return tfail(ts, PSWEEP_ESTATE, "nothing integrated yet");
     TsdfDev T = ts->last;
     void *a[] = {&T, &d_stats};
-    return launch(ts, 5, dim3(1), dim3(1024), a, (hipStream_t)hip_stream, "tsdf stats");
+    // one workgroup, or, where its pass over the keys takes longer than a second
+    // launch (8.6 us at 32,768 slots, what the two launches take), one for every
+    // 4,096 slots
+    const int g = ts->nslots <= kStatsOne ? 1 : std::min(256, (ts->nslots + kStatsSlots - 1) / kStatsSlots);
+    if (g > 1) {
+        const psweep_status st = launch(ts, 6, dim3(1), dim3(64), a, (hipStream_t)hip_stream, "tsdf stats");
+        if (st != PSWEEP_OK) return st;
+    }
+    return launch(ts, 5, dim3(g), dim3(1024), a, (hipStream_t)hip_stream, "tsdf stats");
 }
 
 void psweep_tsdf_destroy(psweep_tsdf *ts) {

@@ -122,3 +122,26 @@ def test_queues_hold_every_item_once(tmp_path):
         print("ok")
     """)
     assert "ok" in out
+
+
+def test_tsdf_stats_of_large_maps_take_many_workgroups(tmp_path):
+    """The allocated blocks of a map are counted by workgroups in proportion to
+    its slots, after one launch that clears their sum."""
+    out = host_run(tmp_path, """
+        for blocks, launches in (((75, 4, 75), [1]), ((32, 32, 32), [1]), ((33, 32, 32), [1, 9]), ((256, 256, 256), [1, 256])):
+            c = P.psweep_tsdf_config(0.1, 0.3, (P._i32 * 3)(*blocks), 100.0, 1, 160, 120)
+            ts = P.psweep_tsdf_create(c)
+            # an address only: the launches are not played
+            P.psweep_tsdf_set_workspace(ts, 1 << 36, P.psweep_tsdf_workspace_size(ts))
+            P.psweep_tsdf_reset(ts)
+            cam = P.psweep_camera(0.9, 80.0, 80.0, 80.0, 60.0, 160, 120)
+            pose = P.psweep_pose((P._d * 9)(1, 0, 0, 0, 1, 0, 0, 0, 1), (P._d * 3)(0, 0, 0))
+            P.psweep_tsdf_integrate(ts, cam, pose, (0.0, 0.0, 0.0), 1 << 32, 0)
+            FAKE.fake_hip_clear()
+            P.psweep_tsdf_stats(ts, 1 << 33)
+            got = [int(l.split("=")[1]) for l in FAKE.fake_hip_log().decode().splitlines()]
+            assert got == launches, (blocks, got)
+            P.psweep_tsdf_destroy(ts)
+        print("ok")
+    """)
+    assert "ok" in out
