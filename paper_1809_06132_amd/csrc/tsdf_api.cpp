@@ -219,7 +219,8 @@ psweep_status psweep_tsdf_extract(psweep_tsdf *ts, float *d_tsdf, float *d_weigh
     if (!ts->integrated) return tfail(ts, PSWEEP_ESTATE, "nothing integrated yet");
     TsdfDev T = ts->last;
     void *a[] = {&T, &d_tsdf, &d_weight, &d_block_count};
-    const long long g = ((long long)T.nb[1] * T.nb[2] * 64 + 3) / 4;   // four rows of voxels a workgroup
+    const int per = 4 * psw::tsdf_extract_rows(T.nb[0]);   // rows of voxels a workgroup
+    const long long g = ((long long)T.nb[1] * T.nb[2] * 64 + per - 1) / per;
     return launch(ts, 4, dim3(g < 65536 ? (unsigned)g : 65536u), dim3(256), a, (hipStream_t)hip_stream, "tsdf extract");
 }
 

@@ -28,4 +28,8 @@ struct TsdfDev {
     float *D, *W;               // [slot][512]
 };
 
+// rows of voxels that a wave of 64 lanes copies out at a time, half a block's
+// row per lane
+__host__ __device__ inline int tsdf_extract_rows(int blocks_x) { return blocks_x < 32 ? 64 / (2 * blocks_x) : 1; }
+
 }  // namespace psw

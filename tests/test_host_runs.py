@@ -145,3 +145,26 @@ def test_tsdf_stats_of_large_maps_take_many_workgroups(tmp_path):
         print("ok")
     """)
     assert "ok" in out
+
+
+def test_tsdf_extraction_fills_its_waves_in_narrow_boxes(tmp_path):
+    """The copy of a box takes a lane per half a block's row: rows of few blocks
+    share a wave, so that the workgroups go down with them."""
+    out = host_run(tmp_path, """
+        for blocks in ((1, 64, 64), (2, 64, 64), (3, 5, 7), (16, 8, 8), (17, 8, 8), (32, 8, 8), (75, 4, 75)):
+            c = P.psweep_tsdf_config(0.1, 0.3, (P._i32 * 3)(*blocks), 100.0, 1, 160, 120)
+            ts = P.psweep_tsdf_create(c)
+            P.psweep_tsdf_set_workspace(ts, 1 << 36, P.psweep_tsdf_workspace_size(ts))
+            P.psweep_tsdf_reset(ts)
+            cam = P.psweep_camera(0.9, 80.0, 80.0, 80.0, 60.0, 160, 120)
+            pose = P.psweep_pose((P._d * 9)(1, 0, 0, 0, 1, 0, 0, 0, 1), (P._d * 3)(0, 0, 0))
+            P.psweep_tsdf_integrate(ts, cam, pose, (0.0, 0.0, 0.0), 1 << 32, 0)
+            FAKE.fake_hip_clear()
+            P.psweep_tsdf_extract(ts, 1 << 33, 1 << 34, 1 << 35)
+            got = [int(l.split("=")[1]) for l in FAKE.fake_hip_log().decode().splitlines()]
+            rows, per_wave = blocks[1] * blocks[2] * 64, max(1, 64 // (2 * blocks[0]))
+            assert got == [-(-rows // (4 * per_wave))], (blocks, got)
+            P.psweep_tsdf_destroy(ts)
+        print("ok")
+    """)
+    assert "ok" in out
