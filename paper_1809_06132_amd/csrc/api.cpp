@@ -703,10 +703,10 @@ int resident_blocks(psweep_ctx *ctx, const KernelEntry *e) {
     return n;
 }
 
-// How many chunks the planes of a level are cut into (automatic count): of at
-// least 4 planes each.  An item costs about three of its (plane, source) steps
-// beside its own work (set-up, first warp, partial state), so that few long
-// items are the least work, but too few leave CUs idle at the end of a launch.
+// How many chunks the planes of a level are cut into (automatic count).  An item
+// costs about three of its (plane, source) steps beside its own work (set-up,
+// first warp, partial state), so that few long items are the least work, but too
+// few leave CUs idle at the end of a launch.
 //
 // Item queues: about sqrt(P S n_cu / (3 tiles)) chunks balance the two (whole
 // runs: 360 tiles of 94 planes, 3 sources, 265 us with 3 chunks and 190 with 8;
@@ -715,22 +715,35 @@ int resident_blocks(psweep_ctx *ctx, const KernelEntry *e) {
 // no longer shows: ten a CU, of at most 64 planes (912 tiles of 192 planes,
 // 710 us with 3 chunks and 739 with 8; 7,200 of 256, 15.0 ms with 1, 12.7 with 4).
 //
-// A grid per job, largest items first: sqrt(P S n_cu / (2 tiles)), 4 to 8 (748
-// tiles of 80 planes, 1 source, window 5: 120 us with 4, 125 with 6, 150 with 8;
-// 434 of 60, 2 sources, window 13: 155 with 6, 170 with 4; 240 of 64, 2 sources,
-// window 11: 115 with 8, 123 with 6; 153 of 149, 3 sources: 175 with 8, 189 with 6).
+// A grid per job, largest items first: r = sqrt(P S n_cu / (2 tiles)), at least 4
+// (748 tiles of 80 planes, 1 source, window 5: 120 us with 4, 125 with 6, 150 with
+// 8; 434 of 60, 2 sources, window 13: 155 with 6, 170 with 4; 240 of 64, 2
+// sources, window 11: 115 with 8, 123 with 6; 153 of 149, 3 sources: 175 with 8,
+// 189 with 6), but two where r is 2.5 or less (1,320 tiles of 48 planes, window 5,
+// r 2.2: 124 us with 2, 126 with 4; 2,025 of 48, r 1.7: 170 and 186) and one below
+// 1.6 (816 of 16, r 1.58: 51 with 1, 59 with 4; 3,360 of 16, r 0.8: 109 and 227;
+// 6,656 of 48, r 0.96: 381 and 616).
+//
+// Chunks have at least four planes; two while a CU then has three items at most,
+// one while it has two, since in a run that leaves the chip empty a chunk's length
+// is the run's (replayed graphs: 3 tiles of 8 planes, 3 sources, window 9, 50 us
+// in one chunk, 36 in two, 23.6 in eight; 96 of 16, 37.9 in four, 35.6 in eight;
+// but 360 of 8, 47.3 in two and 56.9 in four).  Three steps or fewer stay whole.
 int plane_chunks(const psweep_ctx *ctx, int64_t tiles, int P, int S, bool queues) {
-    const int most = std::max(1, std::min(kMaxChunks, P / 4));
-    if (tiles <= 0) return 1;
+    if (tiles <= 0 || P * S <= 3) return 1;
+    const int64_t fill = std::max<int64_t>(std::min<int64_t>(P / 2, 3 * ctx->n_cu / tiles), 2 * ctx->n_cu / tiles);
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>({kMaxChunks, P, std::max<int64_t>(P / 4, fill)}));
     const double work = (double)P * S * ctx->n_cu / tiles;
     int64_t nch;
     if (queues) {
-        nch = std::min<int64_t>(most, std::lround(std::sqrt(work / 3.0)));
-        if (tiles * nch > 24LL * ctx->n_cu) nch = std::max<int64_t>((10LL * ctx->n_cu + tiles - 1) / tiles, (P + 63) / 64);
+        nch = std::lround(std::sqrt(work / 3.0));
+        if (tiles * std::min(nch, most) > 24LL * ctx->n_cu)
+            nch = std::max<int64_t>((10LL * ctx->n_cu + tiles - 1) / tiles, (P + 63) / 64);
     } else {
-        nch = std::max<int64_t>(4, std::min<int64_t>(most, (int64_t)std::ceil(std::sqrt(work / 2.0))));
+        const double r = std::sqrt(work / 2.0);
+        nch = r < 1.6 ? 1 : r <= 2.5 ? 2 : std::max<int64_t>(4, (int64_t)std::ceil(r));
     }
-    return (int)std::max<int64_t>(1, std::min<int64_t>(nch, most));
+    return (int)std::max<int64_t>(1, std::min(nch, most));
 }
 
 // The plane chunks of level l in a run of `tiles` tiles (of the level, or of the

@@ -71,3 +71,31 @@ def test_persistent_config_matches_a_launch_per_job(w, h, n_src, storage, levels
         for f, m in enumerate(maps):
             for name in m:
                 assert np.array_equal(want[f][name], m[name], equal_nan=True), (key, f, name)
+
+
+@pytest.mark.parametrize("w,h,n_src,nf,ng,window,launch", [
+    (64, 48, 3, 8, 0, 9, "grid"), (64, 48, 3, 8, 0, 9, "persistent"), (97, 61, 4, 2, 0, 5, "grid"), (160, 120, 2, 4, 2, 11, "grid"),
+    (150, 90, 1, 5, 3, 7, "persistent"), (320, 256, 3, 16, 0, 13, "grid"), (640, 480, 1, 4, 2, 9, "grid"),
+])
+def test_automatic_chunks_match_one_pass(w, h, n_src, nf, ng, window, launch):
+    """The chunks that the library chooses, down to one plane each, against one
+    pass over all planes: the same maps, bit for bit."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1809_06132_amd.sweep import PlaneSweep, frame_to_device
+    fr = _frame(w, h, n_src, window)
+    ps = PlaneSweep(Settings(levels=_one(nf, ng, window), best_k=min(2, n_src)), w, h, n_src, launch=launch)
+    ps.set_cameras(0, fr.ref_cam, fr.src_cams, fr.poses)
+    got = []
+    for chunks in (1, 0):
+        ps.set_chunks(0, chunks)
+        out = ps.alloc_outputs()
+        for t in out["merged"].values():
+            t.fill_(7)
+        ps.run([frame_to_device(fr)], [out])
+        torch.cuda.synchronize()
+        got.append(to_np(out["merged"]))
+    ps.close()
+    assert (got[0]["index"] >= 0).any()
+    for name in got[0]:
+        assert np.array_equal(got[0][name], got[1][name], equal_nan=True), name

@@ -168,3 +168,29 @@ def test_tsdf_extraction_fills_its_waves_in_narrow_boxes(tmp_path):
         print("ok")
     """)
     assert "ok" in out
+
+
+def test_plane_chunks_of_small_and_of_large_runs(tmp_path):
+    """Automatic plane chunks: as short as a plane where the run leaves the chip
+    empty, one or two a tile where its tiles alone fill it several times over."""
+    out = host_run(tmp_path, """
+        def auto(w, h, S, planes, win, **kw):
+            r = Run(config(w, h, S, [(planes, 0.5, 0, win, 1, (0, 0, 0, 0))], **kw), 1 << 32)
+            got = sweeps(r())
+            P.psweep_destroy(r.ctx)
+            assert got[0]["inside"] == 1
+            return got[0]["form"], got[0]["chunks"]
+
+        assert auto(64, 48, 3, 8, 9) == ("grid", 8)
+        assert auto(64, 48, 3, 8, 9, launch=1) == ("queues", 8)
+        assert auto(160, 120, 3, 6, 5) == ("grid", 6)
+        assert auto(96, 64, 4, 2, 9) == ("grid", 2)
+        assert auto(64, 48, 1, 3, 9) == ("grid", 1)         # three steps stay whole
+        assert auto(640, 480, 3, 8, 9) == ("grid", 2)       # 360 tiles
+        assert auto(1024, 768, 1, 16, 5) == ("grid", 1)     # 816 tiles, r 1.58
+        assert auto(1280, 960, 1, 48, 5) == ("grid", 2)     # 1,320 tiles, r 2.2
+        assert auto(1024, 768, 1, 48, 5) == ("grid", 4)     # r 2.7
+        assert auto(2048, 1536, 1, 16, 5) == ("grid", 1)    # 3,360 tiles
+        print("ok")
+    """)
+    assert "ok" in out
