@@ -266,8 +266,8 @@ struct Backward {
         // the reference means of this wave's output rows, for every plane
 #pragma unroll
         for (int i = 0; i < R; ++i) abar[(size_t)(wave * R + i) * kWave + lane] = mean_a[i];
-        // pose terms: FP32 per lane over this chunk's planes, FP64 from the
-        // wave reduction on
+        // pose terms: FP32 per lane over this chunk's planes; the lanes' sums are
+        // added in FP64 at the end
         float acc[S][6];
 #pragma unroll
         for (int s = 0; s < S; ++s)
@@ -556,7 +556,7 @@ struct Backward {
                     rA += a; rB = fmaf(a, abs_[(size_t)r * kWave], rB);
                     rC += ch[(size_t)TYO * kWave]; rE += ch[(size_t)2 * TYO * kWave];
                 }
-                // pose terms of this plane in FP32 (at most RS per lane), then FP64
+                // pose terms of this plane (at most RS per lane)
                 float ps[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                 int pox = 0, poy = 0;
                 unsigned long long *pat = patch + (size_t)s * PH * PW;
@@ -724,8 +724,8 @@ struct Backward {
         // gpart per workgroup (a second kernel adds the workgroups in a fixed
         // order).  Every lane's 6 S values go to LDS (the tile and channels are
         // free: the plane loop ended on a barrier), then 16 lanes add up each
-        // value's, 32 in turn and the 16 by lane shuffles: 41 steps for all of
-        // them, where shuffling every value over every wave takes 6 S times 6.
+        // value's, 32 in turn and the 16 by four lane shuffles: 36 steps for all
+        // of them, where shuffling every value over every wave takes 6 S times 6.
         float *red = reinterpret_cast<float *>(smem);   // [6 S][kRed]
         constexpr int kRed = NW * kWave + 16;           // rows half of the banks apart
         static_assert((size_t)6 * S * kRed * 4 <= lds_tile() + (size_t)(NCH * S + 1) * TYO * kWave * 4, "");

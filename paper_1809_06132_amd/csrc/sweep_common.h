@@ -848,12 +848,14 @@ struct Tile {
 // FP16 staging on the default tile (4 waves of 4 rows) with windows up to 9:
 // held to 128 VGPRs, four waves per SIMD, without spills (left alone, the
 // compiler takes a register more for some and settles for three waves).
-// Windows above 9 on that tile take up to 157, and are held to 128 where a CU's
-// LDS has room for four workgroups (their two row buffers; 600x420, 80 planes:
-// window 11, three sources 262 -> 219 us, float images 276 -> 226; window 15,
-// two sources 217 -> 179 and 228 -> 187), not where it holds three (window 13,
-// three sources 222 -> 279; window 11, four 277 -> 310), nor where they take no
-// more anyway (one source, two at windows 11 and 13: 1 % slower held).
+// Windows above 9 on that tile take more than 128 VGPRs of themselves from
+// S * WIN = 30 on (146 to 159; 117 to 125 below, at 26 and less), and are held to
+// 128 where a CU's LDS has room for four workgroups (their two row buffers;
+// 600x420, 80 planes: window 11, three sources 262 -> 219 us, float images 276 ->
+// 226; window 15, two sources 217 -> 179 and 228 -> 187), not where it holds three
+// (window 13, three sources 222 -> 279; window 11, four 277 -> 310), nor where
+// they take no more anyway (one source, two at windows 11 and 13: 1 % slower
+// held).
 // The other kernels keep the compiler's choice: a cap changes their schedule
 // for the worse (measured on the persistent launch).
 template <int WIN, int R, int NW, int S, int STORE>
