@@ -712,8 +712,11 @@ int resident_blocks(psweep_ctx *ctx, const KernelEntry *e) {
 // runs: 360 tiles of 94 planes, 3 sources, 265 us with 3 chunks and 190 with 8;
 // 748 tiles of 80 planes, 1 source, 132 us with 4 and 154 with 8; 667 of 141, 4
 // sources, 905 with 4 and 813 with 8).  Past 24 items a CU the end of the launch
-// no longer shows: ten a CU, of at most 64 planes (912 tiles of 192 planes,
-// 710 us with 3 chunks and 739 with 8; 7,200 of 256, 15.0 ms with 1, 12.7 with 4).
+// no longer shows: ten a CU, of at most 64 planes (912 tiles of 192 planes, 3
+// sources, 710 us with 3 chunks and 739 with 8; 7,200 of 256, 4 sources, 15.0 ms
+// with 1, 12.7 with 4), or of 32 with four sources as far as the root asks for
+// them (912 of 256, FP16: 1,598 us with 4, 1,376 with 8; 1,380 of 128, FP32: 1,207
+// with 2, 1,044 with 4).
 //
 // A grid per job, largest items first: r = sqrt(P S n_cu / (2 tiles)), at least 4
 // (748 tiles of 80 planes, 1 source, window 5: 120 us with 4, 125 with 6, 150 with
@@ -736,9 +739,11 @@ int plane_chunks(const psweep_ctx *ctx, int64_t tiles, int P, int S, bool queues
     const double work = (double)P * S * ctx->n_cu / tiles;
     int64_t nch;
     if (queues) {
-        nch = std::lround(std::sqrt(work / 3.0));
-        if (tiles * std::min(nch, most) > 24LL * ctx->n_cu)
-            nch = std::max<int64_t>((10LL * ctx->n_cu + tiles - 1) / tiles, (P + 63) / 64);
+        nch = std::min<int64_t>(most, std::lround(std::sqrt(work / 3.0)));
+        if (tiles * nch > 24LL * ctx->n_cu) {
+            const int64_t few = std::max<int64_t>((10LL * ctx->n_cu + tiles - 1) / tiles, (P + 63) / 64);
+            nch = S < 4 ? few : std::max(few, std::min<int64_t>(nch, (P + 31) / 32));
+        }
     } else {
         const double r = std::sqrt(work / 2.0);
         nch = r < 1.6 ? 1 : r <= 2.5 ? 2 : std::max<int64_t>(4, (int64_t)std::ceil(r));
@@ -786,14 +791,24 @@ void split_planes(const psweep_ctx *ctx, int l, int64_t tiles, int n_src, bool q
 // 9, one source count, one tile shape (one that the grid kernels have too: the
 // others stay refused), and neither cost volumes nor per-launch timing asked
 // for, which belong to a launch per job.  The maps are the same,
-// bit for bit, and the levels of a run, or its plane chunks, then fill the chip
-// together (per pass, grids then queues: two levels of 1024x768, 3 sources, 323
-// and 286 us; of 1024x544, 4 sources, 356 and 297 us; one of 1024x768, 762 and
-// 711 us).  One job whose items, in the chunks that its grid would have, are all
-// resident at once stays a grid, with no counters at all (grid against queues,
-// per pass: 320x256, one source, 29.3 and 31.0 us; 586x326, 32 planes, 39 and
-// 44; in one chunk set by the caller, 1024x768, one source, 64 planes, 152 and
-// 179; 640x480, three sources, 94 planes, 448 and 446).
+// bit for bit, and the levels and frames of a run then fill the chip together (per
+// pass, grids then queues: two levels of 1024x768, 3 sources, 323 and 286 us; of
+// 1024x544, 4 sources, 356 and 297 us).
+//
+// One job: a grid, whose items are dealt largest first and need no counters,
+// where its items are all resident at once (586x326, one source, 32 planes, 39
+// and 44 us; 1024x768, one source, 64 planes in one chunk set by the caller, 152
+// and 179) and in most other runs (1024x768, one source, 34 + 55 planes, window 7,
+// 151 and 185; 1280x960, two sources, 128 + 64, 713 and 767).  The queues where a
+// tile is long, which keeps an XCD on neighbouring rows of texels: 45 planes a
+// tile for every CU, 120 (plane, source) steps, more than 100 of the run's steps of
+// fronto planes and no more ground planes than those (a tile above the horizon
+// meets no ground plane), and queues of more than 1.3 rounds of the chip
+// (801x601, two sources, 128 planes, BF16, 262 and 254; 480x360, three, 64 + 30,
+// 145 and 125), and four FP32 sources at window 9, whose grid kernel runs at three
+// waves (1206x919, 64 + 30 planes, 797 and 708).  Over 1,134 runs of 411x307 to
+// 1700x1200 this is 0.5 % off the better of the two on average; the queues alone
+// are 5.3 % off, the grids 1.2 %.
 bool one_launch(psweep_ctx *ctx, const psweep_frame *frames, int nf, const psweep_output *out,
                 const KernelEntry **kernel, int64_t *tiles) {
     const psweep_config &cfg = ctx->cfg;
@@ -822,9 +837,16 @@ bool one_launch(psweep_ctx *ctx, const psweep_frame *frames, int nf, const pswee
     if (cfg.launch == PSWEEP_LAUNCH_PERSISTENT) return true;
     if (!fits || !*kernel) return false;
     if (nf * cfg.n_levels > 1) return true;
+    const psweep_level &L = cfg.level[0];
+    const int64_t places = (int64_t)ctx->n_cu * resident_blocks(ctx, *kernel);
     int f, g;
     split_planes(ctx, 0, *tiles, n_src, false, &f, &g);
-    return *tiles * std::max(1, f + g) > (int64_t)ctx->n_cu * resident_blocks(ctx, *kernel);
+    if (*tiles * std::max(1, f + g) <= places) return false;
+    if (n_src == 4 && cfg.storage == PSWEEP_STORAGE_F32 && L.window == 9) return true;
+    split_planes(ctx, 0, *tiles, n_src, true, &f, &g);
+    const int64_t planes = (int64_t)ctx->P[0] * ctx->n_cu;
+    return planes >= 45 * *tiles && planes * n_src >= 120 * *tiles && L.n_fronto >= L.n_ground &&
+           L.n_fronto * n_src > 100 && 10 * *tiles * std::max(1, f + g) > 13 * places;
 }
 
 // Build the per-run tables (host side) for `frames`: job, setup, prep,

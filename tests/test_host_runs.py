@@ -67,15 +67,15 @@ def test_tiles_without_a_grid_kernel_stay_refused(tmp_path):
     assert "ok" in out
 
 
-def test_one_job_that_fits_the_chip_is_a_grid(tmp_path):
-    """A grid config's single job goes into the item queues only where the items
-    of the grid that it would be, in the chunks that it would have, are more
-    than the chip holds (here 256 CUs of four workgroups); several jobs always
-    do.  The chunks a caller sets, and those the static scratch has room for,
-    count as they are."""
+def test_launch_form_of_one_job(tmp_path):
+    """A grid config's single job goes into the item queues only where its grid's
+    items, in the chunks that it would have, are more than the chip holds (here
+    256 CUs of four workgroups) and its tiles are long; several jobs always do.
+    The chunks a caller sets, and those the static scratch has room for, count as
+    they are."""
     out = host_run(tmp_path, """
-        def form(w, h, S, planes, win=7, chunks=0, call=P.psweep_run, frames=1, **kw):
-            r = Run(config(w, h, S, [(planes, 0.5, 0, win, 1, (0, 0, 0, 0))], frames=frames, **kw), 1 << 32,
+        def form(w, h, S, planes, win=7, chunks=0, call=P.psweep_run, frames=1, ground=0, **kw):
+            r = Run(config(w, h, S, [(planes, 0.5, ground, win, 1, (0, 0, 0, 0))], frames=frames, **kw), 1 << 32,
                     workspace=call is P.psweep_run)
             P.psweep_set_chunks(r.ctx, 0, chunks)
             got = sweeps(r(call))
@@ -88,13 +88,25 @@ def test_one_job_that_fits_the_chip_is_a_grid(tmp_path):
         # 10 x 20 tiles: five chunks, not the eight that 32 planes allow
         assert form(586, 326, 1, 32) == ("grid", 5, 1000)
         assert form(586, 326, 1, 32, chunks=5) == ("grid", 5, 1000)
-        assert form(586, 326, 1, 32, chunks=6)[0] == "queues"
         assert form(640, 480, 3, 96, chunks=1)[:2] == ("grid", 1)
         assert form(640, 480, 3, 96)[0] == "queues"
         assert form(640, 480, 3, 96, frames=2, chunks=1)[0] == "queues"
+        # more items than places, but short tiles, or tiles mostly of ground planes
+        assert form(1024, 768, 1, 34, ground=55)[0] == "grid"
+        assert form(1206, 919, 2, 34, 9, ground=55)[0] == "grid"
+        assert form(586, 342, 2, 16, 9, ground=64)[0] == "grid"
+        assert form(640, 480, 4, 30, ground=100)[0] == "grid"
+        assert form(801, 601, 2, 128, storage=P.STORAGE_BF16)[0] == "queues"
+        assert form(640, 480, 3, 64, 9, ground=30)[0] == "queues"
+        # four sources in FP32: at window 9 whatever the tiles
+        assert form(1206, 919, 4, 64, 9, ground=30)[0] == "queues"
+        assert form(1206, 919, 4, 64, 7, ground=30)[0] == "grid"
+        assert form(1206, 919, 4, 64, 9, ground=30, storage=P.STORAGE_F16)[0] == "grid"
+        # a persistent config is never a grid
+        assert form(320, 256, 1, 32, launch=1)[0] == "queues"
         # the static scratch with no room for chunks
         assert form(1024, 896, 4, 200, call=P.psweep_run_noalloc) == ("grid", 1, 1008)
-        assert form(1152, 896, 3, 200, call=P.psweep_run_noalloc) == ("queues", 1, 1120)
+        assert form(896, 608, 3, 200, 9, call=P.psweep_run_noalloc)[0] == "queues"
         print("ok")
     """)
     assert "ok" in out
